@@ -195,8 +195,7 @@ __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_
     }
     if (rng_fail) atomicExch(a.status, 6);
     const uint64_t bits = res_alive ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max_block(a, bits);
 }
 
 template <int NMAX, bool EXACT, typename CT>

@@ -505,8 +505,7 @@ __device__ __forceinline__ bool z26_grow(const GrowArgs &a, const double *logm, 
     }
     if (rng_fail && !left_box) atomicExch(a.status, 6);
     const uint64_t bits = (res_alive && t == 0) ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max(a, bits);
     return left_box;
 }
 
@@ -754,8 +753,7 @@ __device__ __forceinline__ bool z26_grp_grow(const GrowArgs &a, const double *lo
     }
     if (rng_fail && !left_box) atomicExch(a.status, 6);
     const uint64_t bits = (res_alive && t == 0) ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max(a, bits);
     return left_box;
 }
 
@@ -1063,8 +1061,7 @@ __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint
     }
     if (rng_fail) atomicExch(a.status, 6);
     const uint64_t bits = res_alive ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max_block(a, bits);
 }
 
 template <bool EXACT, typename CT>

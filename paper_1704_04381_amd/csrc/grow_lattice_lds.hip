@@ -384,8 +384,7 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
     }
     if (rng_fail && !left_box) atomicExch(a.status, 6);
     const uint64_t bits = (res_alive && t == 0) ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max(a, bits);
     return left_box;
 }
 
@@ -645,8 +644,7 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
     }
     if (rng_fail && !left_box) atomicExch(a.status, 6);
     const uint64_t bits = (res_alive && t == 0) ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if ((threadIdx.x & 63) == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max(a, bits);
     return left_box;
 }
 

@@ -537,8 +537,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
     }
     if (rng_fail) atomicExch(a.status, 6);
     const uint64_t bits = (res_alive && t == 0) ? (uint64_t)__double_as_longlong(res_lw) : 0ull;
-    const uint64_t wmax = wave_max_u64(bits);
-    if (lane == 0 && wmax != 0) atomicMax(a.log_w_max_bits, (unsigned long long)wmax);
+    publish_log_w_max(a, bits);
 }
 
 template <int G>

@@ -161,6 +161,39 @@ struct GrowArgs {
     double logm[65];                    // ln(m) correctly rounded, m = 0..64
 };
 
+// Raises the ensemble's max log W cell to `bits` (the bit pattern of log W >= 0,
+// 0 for none), one value per lane, all 64 lanes active.  Atomics on one cell
+// complete one at a time, 11-14 ns each however many waves issue them (1.77 ms
+// for the 156,000 waves of 10^7 chains, as long as their growth), while reads
+// of it are served in parallel: a wave whose maximum is not above the value it
+// reads (a lower bound of the cell, which only rises) issues no atomic.
+__device__ __forceinline__ void publish_log_w_max(const GrowArgs &a, uint64_t bits)
+{
+    unsigned long long *cell = a.log_w_max_bits;
+    const uint64_t seen = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t wmax = wave_max_u64(bits);
+    if ((threadIdx.x & 63) == 0 && wmax > seen) atomicMax(cell, (unsigned long long)wmax);
+}
+
+// The same for kernels whose short waves end together (one lane per chain):
+// the four waves of a 256-thread block combine their maxima first, so that a
+// small grid, whose blocks all read 0, issues a quarter of the atomics.
+// Every thread of the block calls this.
+__device__ __forceinline__ void publish_log_w_max_block(const GrowArgs &a, uint64_t bits)
+{
+    __shared__ uint64_t wmax[4];
+    const uint64_t w = wave_max_u64(bits);
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long *cell = a.log_w_max_bits;
+        const uint64_t seen = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t m = wmax[0];
+        for (int q = 1; q < 4; ++q) m = wmax[q] > m ? wmax[q] : m;
+        if (m > seen) atomicMax(cell, (unsigned long long)m);
+    }
+}
+
 // One ensemble of a batched launch: its arguments and, for the LDS lattice
 // kernel, its plane length H and chain stride S (words).
 struct GrowEntry {
