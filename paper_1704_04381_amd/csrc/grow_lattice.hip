@@ -1,31 +1,28 @@
 // Lattice chain growth on the simple cubic lattice (Sec. 3.3.2, Algorithm 1;
-// weight of Eq. 3), one chain per lane, chain state in VGPRs.
+// weight of Eq. 3), one chain per lane, chain state in VGPRs: one history
+// word per monomer (lattice_common.hpp), fully unrolled over NMAX.
+// Coordinates of an N <= 64 chain stay in [-63, 63], so the coordinate bytes
+// never wrap and never become zero.
 //
-// Monomer word (one 32-bit VGPR per monomer, fully unrolled over NMAX):
-//   byte 0 : Q = x + 2y + 3z  (mod 256)
-//   byte 1 : x + 128,  byte 2 : y + 128,  byte 3 : z + 128
-// Coordinates of an N <= 64 chain stay in [-63, 63], so bytes 1..3 never
-// wrap and never become zero.
+// Step i (tip t = monomer i-1) tests the earlier monomers of the parity that
+// can touch the tip, j = i-4, i-6, ..., two operations each; j = i-2 is the
+// tip's bonded neighbour, so its direction bit is taken untested.  The free
+// mask and the picked rank address one LDS table entry: the move and the
+// increment of the counts n_m.  An empty mask (a dead end) has a zero entry,
+// so a dead chain needs no selects: its mask is kept empty by `alive`.
 //
-// Pair test of step i (tip t = monomer i-1), for each earlier monomer j of the
-// parity that can touch the tip's neighbours (j = i-2, i-4, ...; the cubic
-// lattice is bipartite, so the other parity never neighbours the tip):
-//   L    = v_msad_u8(r_j, t & ~0xFF)   L1 distance; byte 0 is masked because
-//                                      the reference byte is zero
-//   bit  = sat(2 - L)                  1 iff r_j is a neighbour of t
-//   code = (Q_j - Q_t + 3) mod 32      = 0..6 without 3: -z, -y, -x, +x, +y, +z
-//   occ |= bit << code                 v_lshl_or_b32
-// Four VALU operations per pair, no memory access.  The six neighbour codes
-// are also the candidates' canonical order, so free = ~occ & 0x77 is already
-// the ordered candidate mask and the pick is one LDS table lookup.
+// log W = sum over m of n_m log m (Eq. 3 grouped by value): the counts are
+// 6-bit fields of one register, m = 2..5 at 0, 6, 12, 18, m = 1 at 26, and
+// the one m = 6 (step 1) at bit 24; the sum is formed once after the last
+// step, and the fields add up to the number of monomers placed.  Coordinate
+// sums run along with the steps (of a dead chain too: its repeated last
+// monomer is taken out at the end).
 //
-// log W = sum over m of n_m log m (Eq. 3 grouped by value): the counts of
-// m = 2..5 are kept as 6-bit fields of one register (2 operations per step)
-// and the sum is formed once after the last step.
-//
-// Measured on MI355X (10^7 chains, N = 64): splitting the occupied mask over
-// two accumulators shortens the per-step dependency chain and gains ~10%;
-// capping the kernel at 4 waves per SIMD (spilling) loses ~10%.
+// Bound by VALU issue: 4,264 instructions per wave and N = 64 chain, where the
+// four-operation test with its per-step selects took 6,888.  MI355X, N = 64,
+// 10^7 chains, growth kernel: 1.83 -> 1.03 ms (with the max-log-W atomics out
+// of the way).  At least 4 waves per SIMD (128 VGPRs, against the 141 the
+// compiler takes by itself): 1.03 against 1.06 ms.
 #include "lattice_common.hpp"
 
 #include <type_traits>
@@ -43,14 +40,15 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
-constexpr uint32_t kOrigin = 0x80808000u; // origin, Q = 0
-
 template <int NMAX, bool EXACT, typename CT>
 __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_t bid)
 {
-    __shared__ uint32_t lut[kLutSize];
+    __shared__ uint2 lut[kByteLutSize]; // move, increment of the n_m fields
     __shared__ double logm[8];
-    for (int t = threadIdx.x; t < kLutSize; t += blockDim.x) lut[t] = lattice_move((uint32_t)t);
+    for (uint32_t t = threadIdx.x; t < kByteLutSize; t += blockDim.x) {
+        const uint32_t m = __builtin_popcount((t >> 2) & kByteDirs);
+        lut[t] = make_uint2(byte_move(t), m ? 1u << ((6u * m + 20u) & 31u) : 0u);
+    }
     if (threadIdx.x < 8) logm[threadIdx.x] = a.logm[threadIdx.x];
     __syncthreads();
 
@@ -59,12 +57,9 @@ __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_
     const uint64_t g = a.chain_offset + c;
     const int N = a.n_monomers;
 
-    uint32_t pos[NMAX];
-    static_for<0, NMAX>([&](auto J) { pos[J.value] = kOrigin; });
-    uint32_t tip = kOrigin;
-    bool alive = false;
-    int grown = 1;
-    uint32_t cntp = 0;
+    uint32_t pos[NMAX]; // history words
+    static_for<0, NMAX>([&](auto J) { pos[J.value] = 0u; });
+    pos[0] = byte_history(kByteOrigin);
     uint64_t wx = 1;
     bool rng_fail = false;
     Philox4 blk{0, 0, 0, 0};
@@ -79,33 +74,28 @@ __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_
     bool pending = valid;
 
     for (uint32_t rd = 0; rd < a.max_rounds; ++rd) {
-        if (rd > 0) {
-            static_for<0, NMAX>([&](auto J) { pos[J.value] = pending ? kOrigin : pos[J.value]; });
-            tip = pending ? kOrigin : tip;
-            cntp = pending ? 0u : cntp;
-            wx = pending ? 1ull : wx;
-        }
-        alive = pending;
-        grown = 1;
+        uint32_t tip = kByteOrigin;
+        uint32_t alive = pending ? ~0u : 0u;
+        uint32_t cnt = 0;
+        // biased coordinate sums over the monomers (x and z as 16-bit halves)
+        uint32_t sxz = 0x00800080u, sy = 0x00008000u, s2 = 3u * 128u * 128u;
+        if (EXACT) wx = 1;
         const uint32_t hi = rd << 16; // attempt in the high half of the step word
 
         static_for<1, NMAX>([&](auto I) {
             constexpr int i = I.value;
             if (i >= N) return;
-            // occupied-neighbour mask from the same-parity monomers, accumulated
-            // in two independent registers to halve the dependency chain
-            const uint32_t tref = tip & 0xFFFFFF00u;
-            const uint32_t tq = tip - 3u;
-            uint32_t occ = 0, occ2 = 0;
-            static_for<0, i / 2>([&](auto Q) {
-                constexpr int j = i - 2 - 2 * Q.value;
-                const uint32_t L = __builtin_amdgcn_msad_u8(pos[j], tref, 0u);
-                const uint32_t bit = __builtin_elementwise_sub_sat(2u, L);
-                if constexpr (Q.value & 1) occ2 = (bit << ((pos[j] - tq) & 31u)) | occ2;
-                else occ = (bit << ((pos[j] - tq) & 31u)) | occ;
+            // directions of the occupied neighbours; two accumulators halve
+            // the dependency chain
+            const uint32_t tref = tip & kByteCoords;
+            uint32_t acc = 0, acc2 = 0;
+            if constexpr (i >= 2) acc = pos[i - 2];
+            static_for<0, (i >= 4 ? i / 2 - 1 : 0)>([&](auto Q) {
+                constexpr int j = i - 4 - 2 * Q.value;
+                if constexpr (Q.value & 1) acc = byte_pair(acc, pos[j], tref);
+                else acc2 = byte_pair(acc2, pos[j], tref);
             });
-            occ |= occ2;
-            const uint32_t freem = ~occ & 0x77u;
+            const uint32_t freem = byte_free(acc | acc2, tip, alive);
             const uint32_t m = __builtin_popcount(freem);
 
             // 16-bit selection word: half i mod 8 of one Philox block per 8 steps
@@ -116,64 +106,56 @@ __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_
             const uint32_t x = (h & 1) ? (wd >> 16) : (wd & 0xFFFFu);
             const uint32_t p = x * m;
             uint32_t r = p >> 16;
-            if (__builtin_expect(alive && (p & 0xFFFFu) < m, 0)) {
+            if (__builtin_expect((p & 0xFFFFu) < m, 0)) { // never for m = 0
                 r = lemire_redraw16(a.seed, g, (uint32_t)i | hi, m, x);
                 if (r == kPickFailed) {
                     rng_fail = true;
                     r = 0;
                 }
             }
-
-            const bool step_ok = alive && m != 0;
-            const uint32_t mv = lut[(freem << 3) | (r & 7u)];
-            const uint32_t nxt = ((tip & 0xFFFFFF00u) + (mv & 0xFFFFFF00u)) | ((tip + mv) & 0xFFu);
-            if (alive && m == 0) {
-                alive = false;
-                grown = i;
-            }
-            tip = step_ok ? nxt : tip;
-            pos[i] = tip;
-            if (step_ok) {
-                // n_m field at bit 6 (m - 2) mod 32: m = 2..5 at 0, 6, 12, 18, m = 1
-                // at 26 (unused); step 1 always has m = 6 and is not counted
-                if constexpr (i >= 2) cntp += 1u << ((6u * m + 20u) & 31u);
-                if (EXACT) wx = wx * (uint64_t)m;
-            }
+            const uint2 mv = lut[(freem << 2) | r]; // r < m <= 6, or 0
+            tip += mv.x;
+            cnt += mv.y;
+            alive = m != 0 ? ~0u : 0u;
+            if (EXACT) wx = wx * (uint64_t)m;
+            const uint32_t co = tip & kByteCoords;
+            sxz += co & 0x00FF00FFu;
+            sy += co & 0x0000FF00u;
+            s2 = __builtin_amdgcn_udot4(co, co, s2, false);
+            if constexpr (i + 2 < NMAX) pos[i] = byte_history(tip);
         });
-        if (alive) grown = N;
-        const bool ends = pending && (alive || rd + 1 >= a.max_rounds);
+        const bool done = alive != 0u;
+        const bool ends = pending && (done || rd + 1 >= a.max_rounds);
         if (ends) {
+            const uint32_t n2 = cnt & 63u, n3 = (cnt >> 6) & 63u, n4 = (cnt >> 12) & 63u, n5 = (cnt >> 18) & 63u;
+            const int grown = 1 + (int)(n2 + n3 + n4 + n5 + (cnt >> 26) + ((cnt >> 24) & 1u));
             // log W = sum over m = 1..6, ascending, of n_m log m (one rounding
             // each); n_1 log 1 = 0 and m_1 = 6 always
             double lw = 0.0;
             if (N >= 2) {
-                lw = lw + (double)(cntp & 63u) * logm[2];
-                lw = lw + (double)((cntp >> 6) & 63u) * logm[3];
-                lw = lw + (double)((cntp >> 12) & 63u) * logm[4];
-                lw = lw + (double)((cntp >> 18) & 63u) * logm[5];
+                lw = lw + (double)n2 * logm[2];
+                lw = lw + (double)n3 * logm[3];
+                lw = lw + (double)n4 * logm[4];
+                lw = lw + (double)n5 * logm[5];
                 lw = lw + logm[6];
             }
-            // observables over the g placed monomers, from the biased coordinate bytes
-            uint32_t sx = 0, sy = 0, sz = 0, s2 = 0;
-            static_for<0, NMAX>([&](auto J) {
-                constexpr int j = J.value;
-                const uint32_t w = j < grown ? (pos[j] & 0xFFFFFF00u) : 0u;
-                sx = __builtin_amdgcn_udot4(w, 0x00000100u, sx, false);
-                sy = __builtin_amdgcn_udot4(w, 0x00010000u, sy, false);
-                sz = __builtin_amdgcn_udot4(w, 0x01000000u, sz, false);
-                s2 = __builtin_amdgcn_udot4(w, w, s2, false);
-            });
-            const int64_t gg = grown;
-            const int64_t Sx = (int64_t)sx - 128 * gg, Sy = (int64_t)sy - 128 * gg, Sz = (int64_t)sz - 128 * gg;
-            const int64_t S2 = (int64_t)s2 - 256 * ((int64_t)sx + (int64_t)sy + (int64_t)sz) + 3 * 16384 * gg;
-            res_nn = gg * S2 - (Sx * Sx + Sy * Sy + Sz * Sz);
-            res_ex = (int32_t)((tip >> 8) & 0xFFu) - 128;
-            res_ey = (int32_t)((tip >> 16) & 0xFFu) - 128;
-            res_ez = (int32_t)(tip >> 24) - 128;
-            res_lw = alive ? lw : -__builtin_huge_val();
-            res_wx = alive ? wx : 0ull;
+            res_ex = (int32_t)(tip & 0xFFu) - 128;
+            res_ey = (int32_t)((tip >> 8) & 0xFFu) - 128;
+            res_ez = (int32_t)((tip >> 16) & 0xFFu) - 128;
+            // observables over the placed monomers: N terms were added, the
+            // last N - grown of them the tip again
+            const int32_t gg = grown, dup = N - grown;
+            const int32_t Sx = (int32_t)(sxz & 0xFFFFu) - 128 * N - dup * res_ex;
+            const int32_t Sy = (int32_t)(sy >> 8) - 128 * N - dup * res_ey;
+            const int32_t Sz = (int32_t)(sxz >> 16) - 128 * N - dup * res_ez;
+            const int32_t B = (int32_t)((sxz & 0xFFFFu) + (sy >> 8) + (sxz >> 16));
+            const int32_t S2 = (int32_t)s2 - 256 * B + 3 * 16384 * N -
+                               dup * (res_ex * res_ex + res_ey * res_ey + res_ez * res_ez);
+            res_nn = (int64_t)gg * S2 - ((int64_t)Sx * Sx + (int64_t)Sy * Sy + (int64_t)Sz * Sz);
+            res_lw = done ? lw : -__builtin_huge_val();
+            res_wx = done ? wx : 0ull;
             res_grown = grown;
-            res_alive = alive;
+            res_alive = done;
             pending = false;
         }
         if (__ballot(pending) == 0) break;
@@ -199,14 +181,16 @@ __device__ __forceinline__ void grow_lattice_reg_body(const GrowArgs &a, uint64_
 }
 
 template <int NMAX, bool EXACT, typename CT>
-__global__ __launch_bounds__(256) void grow_lattice_reg(GrowArgs a, uint64_t base)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+grow_lattice_reg(GrowArgs a, uint64_t base)
 {
     grow_lattice_reg_body<NMAX, EXACT, CT>(a, base + blockIdx.x);
 }
 
 // Batched launch: block b serves the ensemble whose block range holds b.
 template <int NMAX, bool EXACT, typename CT>
-__global__ __launch_bounds__(256) void grow_lattice_reg_batch(const GrowEntry *tab, const uint64_t *block0, int n,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+grow_lattice_reg_batch(const GrowEntry *tab, const uint64_t *block0, int n,
                                                               uint64_t base)
 {
     const uint64_t bid = base + blockIdx.x;

@@ -27,9 +27,8 @@
 // Monomer words.
 //   byte format (N <= 2048 in LDS, N <= 4096 in registers; coordinates
 //     within [-127, 127], exact by construction up to N = 128, kept by the
-//     box and the regrowth below beyond): as in the register kernel, (Q mod 256, x + 128, y + 128,
-//     z + 128); pair test L = msad(r_j, tip & ~0xFF), bit = sat(2 - L),
-//     code = (r_j - tip + 3) mod 32 from the Q byte, 4 operations.
+//     box and the regrowth below beyond): the history words and the
+//     two-operation pair test of lattice_common.hpp.
 //   wide format (LDS beyond, and the regrowth): A = (x + 2^15) | (y + 2^15) << 16 and
 //     B = (64 + Q mod 32) | (z + 2^15) << 16; pair test
 //     L = sad_u16(A_j, A_t) + sad_u16(B_j & 0xFFFF0000, B_t & 0xFFFF0000),
@@ -53,7 +52,6 @@ __device__ __forceinline__ void lattice_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr uint32_t kByteOrigin = 0x80808000u;            // origin, Q = 0
 constexpr uint32_t kWideOriginA = 0x80008000u;           // x = y = 0
 constexpr uint32_t kWideOriginB = 0x80000000u | 64u;     // z = 0, Q = 0
 
@@ -78,20 +76,14 @@ __device__ __forceinline__ uint32_t group_or(uint32_t v)
     return v;
 }
 
-template <bool WIDE>
-__device__ __forceinline__ uint32_t pair_bits(uint32_t wa, uint32_t wb, uint32_t ta, uint32_t tbh,
-                                              uint32_t tq)
+// Pair test of a wide word (A, B) against the tip: the occupied direction as
+// a bit of the 7-bit mask.
+__device__ __forceinline__ uint32_t wide_pair(uint32_t wa, uint32_t wb, uint32_t ta, uint32_t tbh, uint32_t tq)
 {
-    if constexpr (WIDE) {
-        uint32_t L = __builtin_amdgcn_sad_u16(wa, ta, 0u);
-        L = __builtin_amdgcn_sad_u16(wb & 0xFFFF0000u, tbh, L);
-        const uint32_t bit = __builtin_elementwise_sub_sat(2u, L);
-        return bit << ((wb - tq) & 31u);
-    } else {
-        const uint32_t L = __builtin_amdgcn_msad_u8(wa, ta, 0u);
-        const uint32_t bit = __builtin_elementwise_sub_sat(2u, L);
-        return bit << ((wa - tq) & 31u);
-    }
+    uint32_t L = __builtin_amdgcn_sad_u16(wa, ta, 0u);
+    L = __builtin_amdgcn_sad_u16(wb & 0xFFFF0000u, tbh, L);
+    const uint32_t bit = __builtin_elementwise_sub_sat(2u, L);
+    return bit << ((wb - tq) & 31u);
 }
 
 // Byte words hold each coordinate plus 128 in one byte.  Up to N = 128 no
@@ -106,24 +98,35 @@ constexpr int kByteExactN = 128;
 constexpr int kByteBoxedMaxN = 2048;
 constexpr int kRegrowListWords = 65; // count + one slot per chain of a block (<= 64)
 
-// A- and B-word deltas of a byte-format move (coordinate bytes | dQ).
-__device__ __forceinline__ void wide_move(uint32_t mv, uint32_t &da, uint32_t &db)
+// A- and B-word deltas of the move dQ.
+__device__ __forceinline__ void wide_move(int dq, uint32_t &da, uint32_t &db)
 {
-    const int dq = (int)(int8_t)(mv & 0xFFu);
     const int axis = dq < 0 ? -dq : dq;
     const int sg = dq < 0 ? -1 : 1;
     da = axis == 1 ? (uint32_t)sg : (axis == 2 ? (uint32_t)(sg * 65536) : 0u);
     db = (uint32_t)((axis == 3 ? sg * 65536 : 0) + dq);
 }
 
+// True when the tip word's coordinates reach |coordinate| >= edge: bytes
+// b = x + 128 with b < 129 - edge or 255 - b < 128 - edge, as two byte-wise
+// "has a byte below n" tests (exact for n <= 128) on the three bytes and on
+// their complements.
+__device__ __forceinline__ bool byte_out(uint32_t tip, int edge)
+{
+    const uint32_t v = tip & kByteCoords, w = v ^ kByteCoords;
+    const uint32_t lo = (uint32_t)(129 - edge) * 0x010101u;
+    const uint32_t hb = (uint32_t)(128 - edge) * 0x010101u;
+    return ((((v - lo) & ~v) | ((w - hb) & ~w)) & 0x808080u) != 0u;
+}
+
 __device__ __forceinline__ void lattice_lds_luts(uint32_t *lut, uint32_t *lutb, bool wide)
 {
+    static_assert(kLutSize == kByteLutSize, "one table size");
     for (int idx = threadIdx.x; idx < kLutSize; idx += blockDim.x) {
-        const uint32_t mv = lattice_move((uint32_t)idx);
         if (wide)
-            wide_move(mv, lut[idx], lutb[idx]);
+            wide_move(lattice_dq((uint32_t)idx), lut[idx], lutb[idx]);
         else
-            lut[idx] = mv;
+            lut[idx] = byte_move((uint32_t)idx);
     }
 }
 
@@ -173,7 +176,7 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
         }
         lattice_wave_sync();
         if (pending && t == 0) {
-            base[0] = ta;
+            base[0] = WIDE ? ta : byte_history(ta);
             if constexpr (WIDE) base[H] = tb;
         }
         lattice_wave_sync();
@@ -187,15 +190,22 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
             const uint32_t *pb = pa + H;
             const int nrel = i >> 1;
             const int passes = (nrel + 4 * G - 1) / (4 * G);
-            const uint32_t tref = WIDE ? ta : (ta & 0xFFFFFF00u);
+            const uint32_t tref = WIDE ? ta : (ta & kByteCoords);
             const uint32_t tbh = tb & 0xFFFF0000u;
-            const uint32_t tq = (WIDE ? tb : ta) - 3u;
+            const uint32_t tq = tb - 3u;
             uint32_t occ = 0, occ2 = 0;
             const auto test4 = [&](const uint4 &wa, const uint4 &wb) {
-                occ |= pair_bits<WIDE>(wa.x, wb.x, tref, tbh, tq);
-                occ2 |= pair_bits<WIDE>(wa.y, wb.y, tref, tbh, tq);
-                occ |= pair_bits<WIDE>(wa.z, wb.z, tref, tbh, tq);
-                occ2 |= pair_bits<WIDE>(wa.w, wb.w, tref, tbh, tq);
+                if constexpr (WIDE) {
+                    occ |= wide_pair(wa.x, wb.x, tref, tbh, tq);
+                    occ2 |= wide_pair(wa.y, wb.y, tref, tbh, tq);
+                    occ |= wide_pair(wa.z, wb.z, tref, tbh, tq);
+                    occ2 |= wide_pair(wa.w, wb.w, tref, tbh, tq);
+                } else {
+                    occ = byte_pair(occ, wa.x, tref);
+                    occ2 = byte_pair(occ2, wa.y, tref);
+                    occ = byte_pair(occ, wa.z, tref);
+                    occ2 = byte_pair(occ2, wa.w, tref);
+                }
             };
             // two passes per iteration, so that the second pass's reads are
             // in flight while the first is tested
@@ -219,7 +229,7 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
             }
             occ |= occ2;
             occ = group_or<G>(occ);
-            const uint32_t freem = ~occ & 0x77u;
+            const uint32_t freem = WIDE ? ~occ & 0x77u : byte_free(occ, ta, ~0u);
             const uint32_t m = __builtin_popcount(freem);
 
             // 16-bit selection word: half i mod 8 of one Philox block per 8 steps
@@ -236,7 +246,7 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
             }
 
             bool step_ok = alive && m != 0;
-            const uint32_t li = (freem << 3) | r; // r < m <= 6, or 0
+            const uint32_t li = (freem << (WIDE ? 3 : 2)) | r; // r < m <= 6, or 0
             uint32_t na, nb = 0u;
             if constexpr (WIDE) {
                 uint32_t da, db;
@@ -244,29 +254,18 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
                     da = lut[li];
                     db = lutb[li];
                 } else {
-                    wide_move(lattice_move(li), da, db);
+                    wide_move(lattice_dq(li), da, db);
                 }
                 na = ta + da;
                 nb = ((tb + db) & 0xFFFF001Fu) | 0x40u;
             } else {
-                const uint32_t mv = lut[li];
-                na = ((ta & 0xFFFFFF00u) + (mv & 0xFFFFFF00u)) | ((ta + mv) & 0xFFu);
+                na = ta + lut[li];
                 // |coordinate| >= E (127, or the launch's byte_box if set;
-                // possible from step E on):
-                // the chain leaves the box here.  Coordinate bytes b = x + 128
-                // with b < 129 - E or 255 - b < 128 - E, as two byte-wise
-                // "has a byte below n" tests (exact for n <= 128) on the
-                // three bytes and on their complements.
-                if (boxed && i >= edge) {
-                    const uint32_t v = na >> 8, w = v ^ 0xFFFFFFu;
-                    const uint32_t lo = (uint32_t)(129 - edge) * 0x010101u;
-                    const uint32_t hi = (uint32_t)(128 - edge) * 0x010101u;
-                    const uint32_t edge = (((v - lo) & ~v) | ((w - hi) & ~w)) & 0x808080u;
-                    if (step_ok && edge != 0u) {
-                        step_ok = false;
-                        alive = false;
-                        left_box = true;
-                    }
+                // possible from step E on): the chain leaves the box here
+                if (boxed && i >= edge && step_ok && byte_out(na, edge)) {
+                    step_ok = false;
+                    alive = false;
+                    left_box = true;
                 }
             }
             if (alive && m == 0) {
@@ -283,7 +282,7 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
                 }
                 if (t == 0) {
                     uint32_t *wp = base + (i & 1) * WPM * H + (i >> 1);
-                    wp[0] = na;
+                    wp[0] = WIDE ? na : byte_history(na);
                     if constexpr (WIDE) wp[H] = nb;
                 }
             }
@@ -323,9 +322,9 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
                 z = (int32_t)(wb >> 16) - 32768;
             } else {
                 const uint32_t w = wp[0];
-                x = (int32_t)((w >> 8) & 0xFFu) - 128;
-                y = (int32_t)((w >> 16) & 0xFFu) - 128;
-                z = (int32_t)(w >> 24) - 128;
+                x = (int32_t)(w & 0xFFu) - 128;
+                y = (int32_t)((w >> 8) & 0xFFu) - 128;
+                z = (int32_t)((w >> 16) & 0xFFu) - 128;
             }
             sx += x;
             sy += y;
@@ -349,9 +348,9 @@ __device__ __forceinline__ bool lattice_lds_grow(const GrowArgs &a, const uint32
             ey = (int32_t)(ta >> 16) - 32768;
             ez = (int32_t)(tb >> 16) - 32768;
         } else {
-            ex = (int32_t)((ta >> 8) & 0xFFu) - 128;
-            ey = (int32_t)((ta >> 16) & 0xFFu) - 128;
-            ez = (int32_t)(ta >> 24) - 128;
+            ex = (int32_t)(ta & 0xFFu) - 128;
+            ey = (int32_t)((ta >> 8) & 0xFFu) - 128;
+            ez = (int32_t)((ta >> 16) & 0xFFu) - 128;
         }
         if (pending && left_box) {
             pending = false; // grown again in wide words
@@ -465,6 +464,9 @@ __device__ void regrow_wide(const GrowArgs &a, uint64_t first_chain, bool mine, 
 // 0.52 ms; N = 100, 1.03 -> 0.67 ms; N = 128, 1.36 -> 0.92 ms.  Unbounded,
 // the compiler takes 186 VGPRs (2 waves per SIMD: 4.20 ms at N = 256); at
 // 4 waves it spills in the step loop.
+// With the two-operation pair test of lattice_common.hpp (four operations in
+// the figures above): N = 256, 10^6 chains, 3.38 -> 2.68 ms; N = 2048, 10^5
+// chains, 25.2 -> 21.2 ms; the rest of a step is now the larger part.
 constexpr int kGrpSlots = 32; // slots per lane and plane
 
 template <int G, typename CT>
@@ -507,28 +509,27 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
             ta = kByteOrigin;
             cnt = 0;
         }
-        pe[0] = (pending && t == 0) ? kByteOrigin : pe[0];
+        pe[0] = (pending && t == 0) ? byte_history(kByteOrigin) : pe[0];
         alive = pending;
         grown = 1;
         const uint32_t hi = rd << 16;
 
         const auto step = [&](int i, uint32_t(&pl)[SL]) {
             const int ns = ((i >> 1) + G - 1) / G; // slots holding entries of plane i mod 2
-            const uint32_t tref = ta & 0xFFFFFF00u;
-            const uint32_t tq = ta - 3u;
+            const uint32_t tref = ta & kByteCoords;
             uint32_t occ = 0, occ2 = 0;
 #pragma unroll
             for (int q = 0; q < SL / 4; ++q) {
                 if (4 * q >= ns) break;
-                occ |= pair_bits<false>(pl[4 * q], 0u, tref, 0u, tq);
-                occ2 |= pair_bits<false>(pl[4 * q + 1], 0u, tref, 0u, tq);
+                occ = byte_pair(occ, pl[4 * q], tref);
+                occ2 = byte_pair(occ2, pl[4 * q + 1], tref);
                 if (4 * q + 2 >= ns) break; // a tail of one or two slots
-                occ |= pair_bits<false>(pl[4 * q + 2], 0u, tref, 0u, tq);
-                occ2 |= pair_bits<false>(pl[4 * q + 3], 0u, tref, 0u, tq);
+                occ = byte_pair(occ, pl[4 * q + 2], tref);
+                occ2 = byte_pair(occ2, pl[4 * q + 3], tref);
             }
             occ |= occ2;
             occ = group_or<G>(occ);
-            const uint32_t freem = ~occ & 0x77u;
+            const uint32_t freem = byte_free(occ, ta, ~0u);
             const uint32_t m = __builtin_popcount(freem);
 
             if (i == 1 || (i & 7) == 0) blk = draw(a.seed, g, (uint32_t)(i >> 3) | hi, kSlotSelect, 0);
@@ -544,13 +545,9 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
             }
 
             bool step_ok = alive && m != 0;
-            const uint32_t mv = lut[(freem << 3) | r];
-            const uint32_t na = ((ta & 0xFFFFFF00u) + (mv & 0xFFFFFF00u)) | ((ta + mv) & 0xFFu);
+            const uint32_t na = ta + lut[(freem << 2) | r];
             if (boxed && i >= edge) {
-                const uint32_t v = na >> 8, w = v ^ 0xFFFFFFu;
-                const uint32_t lo = (uint32_t)(129 - edge) * 0x010101u;
-                const uint32_t hb = (uint32_t)(128 - edge) * 0x010101u;
-                const bool out = ((((v - lo) & ~v) | ((w - hb) & ~w)) & 0x808080u) != 0u;
+                const bool out = byte_out(na, edge);
                 left_box = left_box || (step_ok && out);
                 alive = alive && !(step_ok && out);
                 step_ok = step_ok && !out;
@@ -561,7 +558,7 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
             cnt += step_ok ? (1ull << (12u * (m - 1u))) : 0ull;
             const int k = i >> 1;
             const uint32_t old = pl[k / G];
-            pl[k / G] = (step_ok && t == (k & (G - 1))) ? na : old;
+            pl[k / G] = (step_ok && t == (k & (G - 1))) ? byte_history(na) : old;
         };
         for (int i = 1; i < N; i += 2) {
             step(i, po);
@@ -586,9 +583,9 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
         int32_t sx = 0, sy = 0, sz = 0;
         int64_t s2 = 0;
         const auto add = [&](uint32_t w) {
-            const int32_t x = w ? (int32_t)((w >> 8) & 0xFFu) - 128 : 0;
-            const int32_t y = w ? (int32_t)((w >> 16) & 0xFFu) - 128 : 0;
-            const int32_t z = w ? (int32_t)(w >> 24) - 128 : 0;
+            const int32_t x = w ? (int32_t)(w & 0xFFu) - 128 : 0;
+            const int32_t y = w ? (int32_t)((w >> 8) & 0xFFu) - 128 : 0;
+            const int32_t z = w ? (int32_t)((w >> 16) & 0xFFu) - 128 : 0;
             sx += x;
             sy += y;
             sz += z;
@@ -610,9 +607,9 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
         }
         const int64_t gg = grown;
         const int64_t nn = gg * s2 - ((int64_t)sx * sx + (int64_t)sy * sy + (int64_t)sz * sz);
-        const int32_t ex = (int32_t)((ta >> 8) & 0xFFu) - 128;
-        const int32_t ey = (int32_t)((ta >> 16) & 0xFFu) - 128;
-        const int32_t ez = (int32_t)(ta >> 24) - 128;
+        const int32_t ex = (int32_t)(ta & 0xFFu) - 128;
+        const int32_t ey = (int32_t)((ta >> 8) & 0xFFu) - 128;
+        const int32_t ez = (int32_t)((ta >> 16) & 0xFFu) - 128;
         if (pending && left_box) {
             pending = false; // grown again in wide words
         } else if (pending && (alive || rd + 1 >= a.max_rounds)) {
