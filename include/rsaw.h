@@ -554,8 +554,11 @@ rsaw_status rsaw_mapping_list(rsaw_mapping *out, int32_t capacity, int32_t *coun
 
 /*
  * rsaw_mapping_query — the mapping a rsaw_gen_chains call with `cfg` would
- * launch its growth kernel with, written to the host struct *m (n_lo =
- * n_hi = cfg->n_monomers).  Host-only, no device call.  Kernels without a
+ * launch its group kernel with, written to the host struct *m (n_lo =
+ * n_hi = cfg->n_monomers).  Host-only, no device call.  Where the built-in
+ * rule serves long simple cubic chains with the site-set kernel, which has no
+ * mapping, this is the built-in mapping of the scanning kernel that a table
+ * entry would select there.  Kernels without a
  * group mapping report lanes = 1 (one lane per chain: lattice N <= 64, exact
  * weights) or lanes = 64 with lds_bytes = 0 (hard spheres beyond N = 1536,
  * bead planes in HBM).

@@ -788,20 +788,42 @@ static hipError_t lds_shape(int N, bool i16, int G, int threads, GrowVariant *v)
     return lds_shape_fmt(N, i16, G, threads, true, v);
 }
 
-// Variant for 64 < N <= 16384.  Built-in rule (measured on MI355X, 10^4 to
+hipError_t lattice_set_variant(int N, bool i16, GrowVariant *v);
+hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
+                              int n, uint64_t blocks, size_t shmem, hipStream_t s);
+
+// Calls that the site set serves instead of the scanning kernels of this
+// file (unless the tuning table maps the call to one of them).  Its step
+// costs the same at every length, a scan's grows with it; its step also takes
+// about 1.2 times as long when few waves run.  MI355X, kernel time, set
+// against scan: 5 10^5 chains, N = 400, 4.03 / 4.02 ms; N = 512, 5.63 / 5.46;
+// 3 10^5 chains, N = 513, 4.09 / 5.78; N = 640, 4.95 / 7.48; 10^5 chains,
+// N = 2048, 10.8 / 21.2; 5000 chains, N = 10000, 7.1 / 81.  2000 chains:
+// N = 600, 0.29 / 0.23; N = 1000, 0.444 / 0.436; N = 2000, 0.81 / 0.91.
+// Restarts, which the scan's waves repeat for every chain of the wave, 10^5
+// chains: N = 300, 1.61 / 1.18; N = 500, 1.99 / 2.70; N = 600, 2.30 / 5.12.
+static bool use_site_set(const GrowArgs &a)
+{
+    const int N = a.n_monomers;
+    if (N > 1024) return true;
+    return a.n_chains >= 16384 && (N > 512 || (a.max_rounds > 1 && N > 400));
+}
+
+// Variant for 64 < N <= 16384; with `scan`, a scanning kernel's.  Built-in rule (measured on MI355X, 10^4 to
 // 10^6 chains): byte words in the group's registers with 2 lanes per chain
 // up to N = 128, 4 up to 256, 8 up to 512, 16 up to 1024, 32 up to 2048
 // and 64 up to 4096 (the fewest lanes whose 32 slots hold a plane); wide words beyond, 32 lanes in 256-thread blocks
 // while eight chains fit in a CU's LDS, else 64 lanes.
 // Four or more waves per block share the move table when the block fits in
 // half a CU's LDS.  A legal mapping of the tuning table replaces the rule.
-hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v)
+hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v, bool scan)
 {
     const int N = a.n_monomers;
     int tl = 0, tt = 0;
     if (tuned_mapping(0 /* simple cubic lattice */, N, a.k_trials, &tl, &tt) &&
         lds_shape(N, i16, tl, tt, v) == hipSuccess)
         return hipSuccess;
+    if (!scan && use_site_set(a)) return lattice_set_variant(N, i16, v);
     const int G = N <= 128 ? 2 : N <= 256 ? 4 : (N <= 512 ? 8 : (N <= 1024 ? 16 : (N <= 2048 ? 32 : 64)));
     // wide words past N = 4096: eight chains of 32 lanes in one 256-thread
     // block per CU while they fit (N = 2200, before the registers took
@@ -895,9 +917,10 @@ static hipError_t dispatch_lds(const GrowArgs &a, const GrowVariant &v, const Gr
 hipError_t launch_grow_lattice_lds(const GrowArgs &a, bool i16, hipStream_t s)
 {
     GrowVariant v;
-    hipError_t e = lattice_lds_variant(a, i16, &v);
+    hipError_t e = lattice_lds_variant(a, i16, &v, false);
     if (e != hipSuccess) return e;
-    const uint64_t blocks = (a.n_chains + v.cpb - 1) / v.cpb;
+    const uint64_t blocks = variant_blocks(v, a.n_chains);
+    if (v.family == 4) return launch_lattice_set(a, v, nullptr, nullptr, 0, blocks, v.shmem, s);
     return dispatch_lds(a, v, nullptr, nullptr, 0, blocks, v.shmem, s);
 }
 

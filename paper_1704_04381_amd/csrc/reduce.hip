@@ -15,7 +15,8 @@
 
 namespace rsaw {
 
-// Zero the max-log-W cell, the status word and the histogram accumulators.
+// Zero the max-log-W cell, the status word, the chain queue and the histogram
+// accumulators.
 __global__ void reduce_init(unsigned long long *lmax_bits, int32_t *status,
                             unsigned long long *hist_acc, int n_acc)
 {
@@ -23,6 +24,7 @@ __global__ void reduce_init(unsigned long long *lmax_bits, int32_t *status,
     if (t == 0) {
         *lmax_bits = 0ull;
         *status = 0;
+        *queue_cell(status) = 0ull;
     }
     for (int q = t; q < n_acc; q += gridDim.x * blockDim.x) hist_acc[q] = 0ull;
 }
@@ -228,6 +230,7 @@ __global__ void reduce_init_batch(const ReduceEntry *tab, int n, uint64_t base)
     if (threadIdx.x == 0) {
         *e.lmax = 0ull;
         *e.status = 0;
+        *queue_cell(e.status) = 0ull;
     }
     for (int q = threadIdx.x; q < 4 * e.r.bins; q += blockDim.x) e.r.hist_acc[q] = 0ull;
 }

@@ -27,7 +27,9 @@ int real_max_monomers();
 uint32_t real_hbm_slots(int n_monomers, uint64_t n_chains);
 int lattice_lds_max_monomers();
 void lattice_reg_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v);
-hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v);
+hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v, bool scan);
+hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
+                              int n, uint64_t blocks, size_t shmem, hipStream_t s);
 hipError_t real_variant(const GrowArgs &a, GrowVariant *v);
 hipError_t launch_lattice_reg_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                                     int n, uint64_t blocks, hipStream_t s);
@@ -377,6 +379,7 @@ rsaw::GrowArgs grow_args(const rsaw_config *cfg, const rsaw_chain_out &o, const 
     a.n_grown = o.n_grown;
     a.log_w_max_bits = (unsigned long long *)(ws + L.off_lmax);
     a.status = (int32_t *)(ws + L.off_status);
+    a.queue = rsaw::queue_cell(a.status);
     std::memcpy(a.logm, logm_table(), sizeof(a.logm));
     return a;
 }
@@ -476,13 +479,16 @@ rsaw_status gen_impl(const rsaw_config *cfg, const rsaw_chain_out *out, rsaw_sum
 }
 
 // Growth-kernel variant (kernel family, template parameters, block shape)
-// of one ensemble, as its launch would choose it.
-hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::GrowVariant *v)
+// of one ensemble, as its launch would choose it; with `scan`, of the
+// kernels whose lane mapping the tuning table holds.
+hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::GrowVariant *v, bool scan = false)
 {
     rsaw::GrowArgs probe;
     std::memset(&probe, 0, sizeof(probe));
     probe.n_monomers = cfg->n_monomers;
     probe.k_trials = cfg->k_trials;
+    probe.n_chains = cfg->n_chains;
+    probe.max_rounds = (cfg->flags & RSAW_RESTART) ? 65536u : 1u;
     const bool i16 = cfg->coord_type == RSAW_I16;
     if (!L.lattice) return rsaw::real_variant(probe, v);
     if (L.z26) return rsaw::lattice26_variant(probe, L.exact, i16, v);
@@ -490,7 +496,7 @@ hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::Gr
         rsaw::lattice_reg_variant(probe, L.exact, i16, v);
         return hipSuccess;
     }
-    return rsaw::lattice_lds_variant(probe, i16, v);
+    return rsaw::lattice_lds_variant(probe, i16, v, scan);
 }
 
 // Everything the launches of a batch need once its tables are on the device:
@@ -534,6 +540,9 @@ rsaw_status run_batch(const BatchLaunch &B, hipStream_t s)
         else if (v.family == 1)
             e = rsaw::launch_lattice_lds_batch(v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks, G.shmem,
                                                s);
+        else if (v.family == 4)
+            e = rsaw::launch_lattice_set(rsaw::GrowArgs{}, v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks,
+                                         G.shmem, s);
         else if (v.family == 3)
             e = rsaw::launch_lattice26_batch(v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks, G.shmem, s);
         else
@@ -615,7 +624,7 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         const rsaw::GrowVariant &v = var[i];
         const uint64_t cap = 2048 / (uint64_t)v.threads;
         const uint64_t slots = v.shmem ? std::min((uint64_t)(163840 / v.shmem), cap) : cap;
-        const uint64_t blocks = (cfgs[i].n_chains + v.cpb - 1) / v.cpb;
+        const uint64_t blocks = rsaw::variant_blocks(v, cfgs[i].n_chains);
         per_cu[i] = blocks >= slots * (uint64_t)n_cu ? slots : 0;
     }
     auto key = [&](int32_t i) {
@@ -677,7 +686,7 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         gtab[q].H = var[i].H;
         gtab[q].S = var[i].S;
         gb0[q] = b;
-        b += (cfgs[i].n_chains + var[i].cpb - 1) / var[i].cpb;
+        b += rsaw::variant_blocks(var[i], cfgs[i].n_chains);
         G.last = q + 1;
         G.blocks = b;
         G.shmem = std::max(G.shmem, var[i].shmem);
@@ -760,7 +769,9 @@ struct ForceMapping {
     ~ForceMapping() { t_force = false; }
 };
 
-// Mapping a call with cfg launches its growth kernel with (host-only).
+// Mapping of the group kernel for cfg: the tuning table's, or the built-in
+// rule's (host-only).  Where the built-in rule takes the site set instead of
+// a group kernel, this is the mapping a table entry would replace.
 rsaw_status query_mapping(const rsaw_config *cfg, rsaw_mapping *m)
 {
     rsaw_chain_out none{};
@@ -768,7 +779,7 @@ rsaw_status query_mapping(const rsaw_config *cfg, rsaw_mapping *m)
     size_t off = 0;
     layout_ensemble(cfg, none, false, &off, &L);
     rsaw::GrowVariant v;
-    if (ensemble_variant(cfg, L, &v) != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
+    if (ensemble_variant(cfg, L, &v, true) != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
     m->geometry = cfg->geometry;
     m->k_trials = cfg->k_trials;
     m->n_lo = m->n_hi = cfg->n_monomers;
@@ -1244,14 +1255,13 @@ rsaw_status rsaw_autotune(const rsaw_config *base, const int32_t *n_edges, int32
         rsaw_mapping win;
         st = query_mapping(&c, &win);
         if (st != RSAW_OK) break;
-        // the mapping in force (built-in rule or an earlier entry), timed
+        // the kernel in force (built-in rule or an earlier entry), timed
         // first: a candidate replaces it only when it is at least
         // kTuneMargin faster, so that timing noise does not move ensembles
         // away from a mapping that also suits co-scheduled launches
         const rsaw_mapping cur = win;
         double cur_ms = -1.0;
         if (cur.lanes >= 2) {
-            ForceMapping f(cur.lanes, cur.threads);
             st = time_calls(c, &cur_ms);
             if (st != RSAW_OK) break;
         }

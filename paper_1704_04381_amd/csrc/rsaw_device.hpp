@@ -158,6 +158,7 @@ struct GrowArgs {
     // reduction side channels
     unsigned long long *log_w_max_bits; // atomicMax of the bit pattern (log W >= 0)
     int32_t *status;                    // RSAW_E_RNG on a rejection-cap hit
+    unsigned long long *queue;          // next chain of the queued kernels, 0 before the launch
     double logm[65];                    // ln(m) correctly rounded, m = 0..64
 };
 
@@ -233,13 +234,22 @@ inline hipError_t launch_sliced(uint64_t blocks, int threads, F &&launch_one)
 // Launch shape of one growth kernel variant; ensembles with equal kernel,
 // template parameters and block size share one batched launch.
 struct GrowVariant {
-    int family;         // 0 lattice (registers), 1 lattice (LDS), 2 hard spheres, 3 26-neighbour lattice
+    int family;         // 0 lattice (registers), 1 lattice (LDS), 2 hard spheres, 3 26-neighbour lattice,
+                        // 4 lattice (site set)
     int p0, p1, p2;     // template parameters of the family
     int threads;        // threads per block
     int cpb;            // chains per block
     size_t shmem;       // dynamic LDS bytes per block
-    int32_t H, S;       // LDS lattice plane length and chain stride
+    int32_t H, S;       // LDS lattice plane length and chain stride; site set: buckets, chains per block
+    uint32_t max_blocks = 0; // queued kernels: blocks that fill the GPU (0: one per cpb chains)
 };
+
+// Blocks of a launch over n_chains chains.
+inline uint64_t variant_blocks(const GrowVariant &v, uint64_t n_chains)
+{
+    const uint64_t b = (n_chains + v.cpb - 1) / v.cpb;
+    return v.max_blocks && b > v.max_blocks ? v.max_blocks : b;
+}
 
 // Lane mapping (lanes per chain, threads per block) that the tuning table
 // holds for a group-kernel call of this geometry, N and k: the calling

@@ -11,6 +11,13 @@ namespace rsaw {
 constexpr int kNumSums = 8; // S0, S2, wR2, w2R2, w2R2^2, wRg2, w2Rg2, w2Rg2^2
 constexpr int kMaxBins = 256;
 
+// Chain queue of the growth kernels that take chains as they go: a counter in
+// the 256-byte workspace region of the status word, on a cache line of its own.
+__host__ __device__ inline unsigned long long *queue_cell(int32_t *status)
+{
+    return (unsigned long long *)(status + 32);
+}
+
 struct BlockPartial {
     double s[kNumSums];
     uint64_t alive, steps;

@@ -1,0 +1,58 @@
+"""The site-set kernel of long simple cubic chains against the oracle, bit for
+bit (Sec. 3.3.2): the edges of the rule that selects it, chains per wave from
+eight to one, restarts, chain offsets past 2^32, ensembles smaller than a
+wave, several ensembles in a launch, and, with the byte box lowered, chains
+that are grown again without the set.  The calls repeat within a process, so
+the chain queue starts each from zero.  GPU test; calls the HIP library
+through its C ABI.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+import paper_1704_04381_amd as rs
+from test_gpu_parity import _lattice_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _restore():
+    yield
+    rs.set_byte_box(0)
+
+
+@pytest.mark.parametrize("N,M,seed,coord,edge,offset,restart", [
+    (1_025, 1, 201, "i32", 0, 0, False),
+    (1_025, 700, 202, "i16", 0, 0, True),
+    (2_048, 150, 203, "i32", 0, (1 << 32) + 11, False),
+    (513, 16_384, 204, "i16", 0, 0, False),   # the rule's smallest ensemble
+    (401, 16_390, 205, "i32", 0, 0, True),    # its shortest chains
+    (5_000, 25, 206, "i16", 0, 0, False),     # two chains per wave
+    (16_384, 5, 207, "i32", 0, 0, False),     # one chain per wave, the longest
+    (1_100, 90, 208, "i32", 30, 0, False),    # some chains without the set
+    (1_030, 40, 209, "i16", 1, 7, True),      # all of them
+])
+def test_site_set_bit_exact(N, M, seed, coord, edge, offset, restart):
+    rs.set_byte_box(edge)
+    _lattice_case(N, M, seed, coord=coord, bins=64, offset=offset, restart=restart)
+
+
+def test_site_set_in_a_batch():
+    specs = [dict(geometry="lattice", N=1_200, k=6, n_chains=60, seed=211),
+             dict(geometry="lattice", N=3_000, k=6, n_chains=20, seed=212, coord="i16"),
+             dict(geometry="lattice", N=1_026, k=6, n_chains=130, seed=213, restart=True),
+             dict(geometry="lattice", N=300, k=6, n_chains=100, seed=214)]
+    for _ in range(2):
+        print("[gpu] site-set batch", flush=True)
+        res = rs.gen_batch(specs)
+        torch.cuda.synchronize()
+        for sp, (out, s) in zip(specs, res):
+            ref = oracle.gen_lattice(sp["seed"], sp["N"], sp["n_chains"], restart=sp.get("restart", False))
+            np.testing.assert_array_equal(out["n_grown"].cpu().numpy().view(np.uint16), ref["n_grown"])
+            np.testing.assert_array_equal(out["log_w"].cpu().numpy(), ref["log_w"])
+            np.testing.assert_array_equal(out["r_end"].cpu().numpy().astype(np.int32), ref["r_end"])
+            np.testing.assert_array_equal(out["n2rg2"].cpu().numpy(), ref["n2rg2"])
+            assert s["n_alive"] == int(np.isfinite(ref["log_w"]).sum())
