@@ -129,25 +129,9 @@ __device__ __forceinline__ void load_bead(const double *P, int e, double &x, dou
 // Accepted Marsaglia pairs a trial lane keeps ahead of the current step.
 constexpr int kQueue = 4;
 
-// Orders the bead accesses of the lanes of one wave: beads in LDS need the
-// wavefront scope, beads in global memory (one wave per block) the
-// workgroup scope, which waits for the stores before later loads.
-template <bool HBM>
-__device__ __forceinline__ void plane_sync()
-{
-    if constexpr (HBM) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    } else {
-        wave_sync();
-    }
-}
-
-// HBM: the beads of chain `bid` live in global memory, in the region of
-// resident block `slot` (one 64-lane chain per block, row 1, no swizzle).
-template <int G, bool HBM>
-__device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, uint32_t slot = 0)
+// Lockstep kernel: the chains of a block grow step by step together.
+template <int G>
+__device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid)
 {
     extern __shared__ double lds[]; // [N][row] (x, y, z) bead triples, swizzled
 
@@ -157,7 +141,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
     const int swz_mul = G == 64 ? 0 : 32 / G;
     const int swz_mask = cpb - 1;
     const int N = a.n_monomers;
-    double *P = HBM ? a.bead_slots + (size_t)slot * 3 * N : lds;
+    double *P = lds;
     const int t = threadIdx.x & (G - 1);
     const int chb = threadIdx.x / G;
     const int lane = threadIdx.x & 63;
@@ -202,7 +186,6 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
         const int o = 3 * at(0);
         P[o] = 0.0; P[o + 1] = 0.0; P[o + 2] = 0.0;
     }
-    if constexpr (HBM) plane_sync<true>();
     __syncthreads();
 
     double tx = 0.0, ty = 0.0, tz = 0.0;
@@ -353,7 +336,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
             bool blocked = false; // bitwise accumulation keeps the tests branch-free
             const auto test_el = [&](int e) {
                 double x, y, z;
-                load_bead<HBM>(P, e, x, y, z);
+                load_bead<false>(P, e, x, y, z);
                 const double dx = cx - x, dy = cy - y, dz = cz - z;
                 double d2 = dx * dx + dy * dy;
                 d2 = d2 + dz * dz;
@@ -361,7 +344,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
             };
             const auto is_near_el = [&](int e) {
                 double x, y, z;
-                load_bead<HBM>(P, e, x, y, z);
+                load_bead<false>(P, e, x, y, z);
                 const double dx = x - tx, dy = y - ty, dz = z - tz;
                 double d2 = dx * dx + dy * dy;
                 d2 = d2 + dz * dz;
@@ -371,8 +354,8 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
                 // beads i-2 and i-3 (masked before step 2 and 3): reads, one
                 // production round while they are in flight, tests
                 double x2, y2, z2, x3, y3, z3;
-                load_bead<HBM>(P, at(i >= 2 ? i - 2 : 0), x2, y2, z2);
-                load_bead<HBM>(P, at(i >= 3 ? i - 3 : 0), x3, y3, z3);
+                load_bead<false>(P, at(i >= 2 ? i - 2 : 0), x2, y2, z2);
+                load_bead<false>(P, at(i >= 3 ? i - 3 : 0), x3, y3, z3);
                 if (!spread) {
                     round();
                     // keeps the round here, ahead of the tests that wait for the reads
@@ -403,8 +386,8 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
                         const int qb = __builtin_ctzll(u);
                         u &= u - 1;
                         double xa, ya, za, xb, yb, zb;
-                        load_bead<HBM>(P, at(base + qa), xa, ya, za);
-                        load_bead<HBM>(P, at(base + qb), xb, yb, zb);
+                        load_bead<false>(P, at(base + qa), xa, ya, za);
+                        load_bead<false>(P, at(base + qb), xb, yb, zb);
                         const auto hit = [&](double x, double y, double z) {
                             const double dx = cx - x, dy = cy - y, dz = cz - z;
                             double d2 = dx * dx + dy * dy;
@@ -478,7 +461,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
             }
             if (!spread)
                 while (__ballot(starving()) != 0) round();
-            plane_sync<HBM>();
+            wave_sync();
             // long chains: once every chain of the wave has ended (most hard-sphere
             // chains beyond a few hundred beads meet a dead end), the wave leaves
             // the step loop instead of running the remaining steps on dead
@@ -543,7 +526,7 @@ __device__ __forceinline__ void grow_real_body(const GrowArgs &a, uint64_t bid, 
 template <int G>
 __global__ __launch_bounds__(256) void grow_real_tp(GrowArgs a, uint64_t base)
 {
-    grow_real_body<G, false>(a, base + blockIdx.x);
+    grow_real_body<G>(a, base + blockIdx.x);
 }
 
 // Batched launch: block b serves the ensemble whose block range holds b.
@@ -553,15 +536,417 @@ __global__ __launch_bounds__(256) void grow_real_tp_batch(const GrowEntry *tab, 
 {
     const uint64_t bid = base + blockIdx.x;
     const int e = find_segment(block0, n, bid);
-    grow_real_body<G, false>(tab[e].a, bid - block0[e]);
+    grow_real_body<G>(tab[e].a, bid - block0[e]);
 }
 
-// Chains beyond the LDS limit: a persistent grid of one-wave blocks, block s
-// growing chains s, s + grid, s + 2 grid, ... in its own HBM plane region.
+// ---------------------------------------------------------------------------
+// Queued kernel: chains too long for eight of them to a wave's LDS, and those
+// whose beads live in global memory.  G lanes per chain (16, 32 or 64), one
+// wave per block; a group takes its next chain from a queue (a counter in the
+// workspace) as its chain ends, so dead ends, which stop most long hard-sphere
+// chains early, idle a group for at most the rest of eight steps.  i mod 8 is
+// common to the wave, everything else is the group's own.
+//
+// Directions.  With kp = the power of two >= k, a group has PH = G / kp (at
+// most 8) sets of trial lanes: lane t draws trial t mod kp of the steps
+// i = t / kp (mod PH), ahead through a two-entry queue, and owns that trial's
+// candidate when such a step comes.  One production round then serves PH
+// steps of every chain (0.4 rounds per step at PH = 4, where a round per step
+// spread over the attempts of one step took 1.1).
+//
+// Culling as above, over all G lanes; beads i-2 and i-3 stay in registers.
+// Flagged beads are tested by their own group only.  With one chain per wave
+// (G = 64) a full block of 64 beads whose nearest bead is D from the tip is
+// not scanned again before the tip can have come D - (b + sigma) closer, b
+// per step: rounded down by far more than the arithmetic's error.
+// ---------------------------------------------------------------------------
+
+// Smallest of the 64 lanes' non-negative values, in every lane (their bit
+// patterns order like the values).
+__device__ __forceinline__ float wave_min(float v)
+{
+    int x = __float_as_int(v);
+    const auto least = [](int a, int b) { return a < b ? a : b; };
+    x = least(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));
+    x = least(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));
+    x = least(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false));
+    x = least(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false));
+    const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    x = least((int)p[0], (int)p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    return __int_as_float(least((int)q[0], (int)q[1]));
+}
+
+// A double from lane `src` (uniform) of the wave.
+__device__ __forceinline__ double lane_double(double v, int src)
+{
+    const int64_t bits = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)bits, src);
+    const int hi = __builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), src);
+    return __longlong_as_double((int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// Blocks of 64 beads of the longest chain, per lane.
+constexpr int kDueRegs = 4;
+
+// Beads of a chain in global memory that LDS holds as well, the latest ones
+// (a multiple of 64): the blocks scanned at every step are among them.
+constexpr int kRing = 256;
+
+// Doubles between the chains of a block: lanes G .. 2 G - 1 of a half wave
+// read on from the banks of lanes 0 .. G - 1 (3 G mod 32 eight-byte banks).
+__host__ __device__ inline int queue_stride(int N, int G)
+{
+    if (G != 16) return 3 * N;
+    return (3 * N + 15) / 32 * 32 + 16;
+}
+
+template <int G, bool HBM>
+__device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *planes, double *ring)
+{
+    static_assert(!HBM || G == 64, "global planes hold one chain per wave");
+    constexpr int kAhead = 2;
+    const int lane = threadIdx.x & 63;
+    const int t = lane & (G - 1);
+    const int gbase = lane & ~(G - 1);
+    const int N = a.n_monomers;
+    const int k = a.k_trials;
+    int kp = 1;
+    while (kp < k) kp <<= 1;
+    const int PH = G / kp < 8 ? G / kp : 8;
+    const int trial = t & (kp - 1), phase = t / kp;
+    const bool draws = trial < k && phase < PH;
+    const uint64_t kmask = kp == 64 ? ~0ull : (1ull << kp) - 1ull;
+    const uint64_t lower = (1ull << trial) - 1ull;
+    const int stride = queue_stride(N, G);
+    double *P = planes + (lane / G) * stride;
+    const double b = a.bond_length;
+    const double sigma2 = a.sigma2, cull2 = a.cull2;
+    const float reach = sqrtf((float)cull2) * 1.00001f, per_b = 1.0f / (float)b;
+
+    double tx = 0.0, ty = 0.0, tz = 0.0;                       // bead i-1
+    double x2 = 0.0, y2 = 0.0, z2 = 0.0, x3 = 0.0, y3 = 0.0, z3 = 0.0; // beads i-2, i-3
+    double q1[kAhead] = {0.0, 0.0}, q2[kAhead] = {0.0, 0.0};   // accepted pairs
+    int lvl = 0;
+    uint32_t nstep = 1, natt = 0;                              // the next draw
+    int due[kDueRegs] = {0, 0, 0, 0};                          // G = 64: lane l, blocks l, l + 64, ...
+    bool busy = false, alive = false, rng_fail = false;
+    int placed = 1, i0 = 0;
+    uint32_t n_mine = 0; // steps with m = t + 1
+    uint32_t rd = 0;
+    uint64_t c = 0, best = 0;
+    uint64_t next = 0, end = 0; // the wave's chunk of the queue
+    bool drained = false;
+
+    const auto start = [&]() { // the chain's next attempt
+        alive = N > 1;
+        placed = 1;
+        i0 = 0;
+        n_mine = 0;
+        tx = ty = tz = 0.0;
+        x2 = y2 = z2 = x3 = y3 = z3 = 0.0;
+        lvl = 0;
+        nstep = phase == 0 ? (uint32_t)PH : (uint32_t)phase;
+        natt = 0;
+#pragma unroll
+        for (int q = 0; q < kDueRegs; ++q) due[q] = 0;
+        if (t == 0) {
+            P[0] = 0.0; P[1] = 0.0; P[2] = 0.0;
+            if constexpr (HBM) {
+                ring[0] = 0.0; ring[1] = 0.0; ring[2] = 0.0;
+            }
+        }
+    };
+
+    for (;;) {
+        // ended chains, the whole wave taking each in turn
+        const bool ended = busy && !alive;
+        const bool again = ended && placed < N && rd + 1 < a.max_rounds;
+        for (uint64_t todo = __ballot(ended && !again && t == 0); todo; todo &= todo - 1) {
+            const int src = __builtin_ctzll(todo);
+            const double *B = planes + (src / G) * stride;
+            const int n = __builtin_amdgcn_readlane(placed, src);
+            const double gd = (double)n;
+            // coordinate sums in bead order: lanes 0, 1, 2 take x, y, z
+            double s = 0.0;
+            const double *Bc = B + lane % 3;
+#pragma unroll 8
+            for (int j = 0; j < n; ++j) s = s + Bc[3 * j];
+            const double cm = s / gd;
+            const double cmx = lane_double(cm, 0), cmy = lane_double(cm, 1), cmz = lane_double(cm, 2);
+            double acc = 0.0;
+            for (int j0 = 0; j0 < n; j0 += 64) {
+                double x, y, z;
+                load_bead<HBM>(B, min(j0 + lane, n - 1), x, y, z);
+                const double dx = x - cmx, dy = y - cmy, dz = z - cmz;
+                double q = dx * dx + dy * dy;
+                q = q + dz * dz;
+                const int nj = min(64, n - j0);
+                for (int j = 0; j < nj; ++j) acc = acc + lane_double(q, j);
+            }
+            // log W = sum over m = 1..k, ascending, of n_m log m
+            double lw = 0.0;
+            for (int mm = 1; mm <= k; ++mm) {
+                const uint32_t nm = (uint32_t)__builtin_amdgcn_readlane((int)n_mine, src + mm - 1);
+                lw = lw + (double)nm * a.logm[mm];
+            }
+            if (n < N) lw = -__builtin_huge_val();
+            if (lane == src) {
+                double r2 = tx * tx + ty * ty;
+                r2 = r2 + tz * tz;
+                if (a.log_w) a.log_w[c] = lw;
+                if (a.r_end) {
+                    double *o = (double *)a.r_end;
+                    o[c] = tx; o[a.n_chains + c] = ty; o[2 * a.n_chains + c] = tz;
+                }
+                if (a.r2) a.r2[c] = r2;
+                if (a.rg2) a.rg2[c] = acc / gd;
+                if (a.n_grown) a.n_grown[c] = (uint16_t)n;
+                const uint64_t bits = n == N ? (uint64_t)__double_as_longlong(lw) : 0ull;
+                best = bits > best ? bits : best;
+            }
+        }
+        wave_sync();
+        if (ended) {
+            busy = again;
+            if (again) {
+                ++rd;
+                start();
+            }
+        }
+        // groups without a chain take the next ones of the queue
+        for (;;) {
+            const uint64_t want = __ballot(!busy && t == 0);
+            if (want == 0 || drained) break;
+            if (next == end) {
+                unsigned long long v = 0;
+                if (lane == 0) v = atomicAdd(a.queue, (unsigned long long)(64 / G));
+                next = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+                end = next + 64 / G < a.n_chains ? next + 64 / G : a.n_chains;
+                if (next >= a.n_chains) {
+                    drained = true;
+                    break;
+                }
+            }
+            const uint64_t rank = __builtin_popcountll(want & ((1ull << gbase) - 1ull));
+            const uint64_t n = (uint64_t)__builtin_popcountll(want);
+            if (!busy && rank < end - next) {
+                busy = true;
+                c = next + rank;
+                rd = 0;
+                start();
+            }
+            next += n < end - next ? n : end - next;
+        }
+        wave_sync();
+        if (__ballot(busy) == 0) break;
+
+        const uint64_t g = a.chain_offset + c;
+        const uint32_t hi = rd << 16;
+        const Philox4 sel = draw(a.seed, g, (uint32_t)(i0 >> 3) | hi, kSlotSelect, 0);
+#pragma unroll 1
+        for (int e = 0; e < 8; ++e) {
+            const int i = i0 + e;
+            const int ph = e & (PH - 1);
+            const bool act = alive && i > 0; // step 0 places nothing
+            const bool owns = draws && phase == ph;
+            // production rounds until every trial of this step has its pair:
+            // each lane with room tries its next attempt
+            while (__ballot(act && owns && lvl == 0) != 0) {
+                const bool room = alive && draws && lvl < kAhead && nstep < (uint32_t)N;
+                double u1, u2;
+                const bool ok = marsaglia_pair(draw(a.seed, g, nstep | hi, (uint32_t)trial, natt), u1, u2);
+                const bool capped = !ok && natt + 1u == kMaxAttempt;
+                const bool put = room && (ok || capped);
+                rng_fail = rng_fail || (room && capped);
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    const bool here = put && lvl == q;
+                    q1[q] = here ? u1 : q1[q];
+                    q2[q] = here ? u2 : q2[q];
+                }
+                lvl += put ? 1 : 0;
+                nstep += put ? (uint32_t)PH : 0u;
+                natt = put ? 0u : natt + (room ? 1u : 0u);
+            }
+            const double v1 = q1[0], v2 = q2[0];
+            const bool takes = act && owns;
+            q1[0] = takes ? q1[1] : q1[0];
+            q2[0] = takes ? q2[1] : q2[0];
+            lvl -= takes ? 1 : 0;
+            const double s = v1 * v1 + v2 * v2;
+            const double qf = 2.0 * sqrt_unit(1.0 - s); // 1 - s in [2^-53, 1]
+            const double ex = v1 * qf, ey = v2 * qf, ez = 1.0 - 2.0 * s;
+            const double cx = tx + b * ex, cy = ty + b * ey, cz = tz + b * ez;
+
+            const auto overlaps = [&](double x, double y, double z) {
+                const double dx = cx - x, dy = cy - y, dz = cz - z;
+                double d2 = dx * dx + dy * dy;
+                d2 = d2 + dz * dz;
+                return d2 < sigma2;
+            };
+            const auto tip_dist2 = [&](double x, double y, double z) {
+                const double dx = x - tx, dy = y - ty, dz = z - tz;
+                double d2 = dx * dx + dy * dy;
+                d2 = d2 + dz * dz;
+                return d2;
+            };
+            bool blocked = ((i >= 2) & overlaps(x2, y2, z2)) | ((i >= 3) & overlaps(x3, y3, z3));
+            const int nb = act ? i - 3 : 0; // beads 0 .. nb-1 are culled, then tested
+            if constexpr (G == 64) {
+                const int nbu = __builtin_amdgcn_readfirstlane(nb);
+                const int iu = __builtin_amdgcn_readfirstlane(i);
+                // bead base + o of a block; the block's beads, if among the
+                // last kRing, come from LDS
+                const auto bead = [&](int base, int o, double &x, double &y, double &z) {
+                    if (HBM && base + kRing >= iu) load_bead<false>(ring, (base & (kRing - 1)) + o, x, y, z);
+                    else load_bead<HBM>(P, min(base + o, N - 1), x, y, z);
+                };
+                const auto retest = [&](uint64_t u, int base) {
+                    for (; u; u &= u - 1) {
+                        double x, y, z;
+                        bead(base, __builtin_ctzll(u), x, y, z);
+                        blocked = blocked | overlaps(x, y, z);
+                    }
+                };
+#pragma unroll
+                for (int rg = 0; rg < kDueRegs; ++rg) {
+                    if (4096 * rg >= nbu) break;
+                    uint64_t todo = __ballot(due[rg] <= i && 4096 * rg + 64 * lane < nbu);
+                    while (todo) { // two due blocks at a time
+                        const int qa = __builtin_ctzll(todo);
+                        todo &= todo - 1;
+                        const bool two = todo != 0;
+                        const int qb = two ? __builtin_ctzll(todo) : qa;
+                        todo &= todo - 1; // 0 stays 0
+                        const int ba = 4096 * rg + 64 * qa, bb = 4096 * rg + 64 * qb;
+                        double xa, ya, za, xb, yb, zb;
+                        bead(ba, t, xa, ya, za);
+                        bead(bb, t, xb, yb, zb);
+                        const double da = tip_dist2(xa, ya, za), db = tip_dist2(xb, yb, zb);
+                        const uint64_t ua = __ballot(ba + t < nbu && !(da >= cull2)),
+                                       ub = __ballot(two && bb + t < nbu && !(db >= cull2));
+                        retest(ua, ba);
+                        retest(ub, bb);
+                        const auto next_due = [&](double d2, uint64_t u, int b0) {
+                            if (u != 0 || b0 + 64 > nbu) return i + 1;
+                            const float d = __builtin_amdgcn_sqrtf(wave_min((float)d2)) * 0.99999f;
+                            const float n = floorf((d - reach) * per_b - 0.01f);
+                            return i + 1 + (n > 0.0f ? (n < 20000.0f ? (int)n : 20000) : 0);
+                        };
+                        const int na = next_due(da, ua, ba);
+                        due[rg] = lane == qa ? na : due[rg];
+                        if (two) {
+                            const int n2 = next_due(db, ub, bb);
+                            due[rg] = lane == qb ? n2 : due[rg];
+                        }
+                    }
+                }
+            } else {
+                int nbu = __builtin_amdgcn_readlane(nb, 0);
+#pragma unroll
+                for (int q = G; q < 64; q += G) {
+                    const int o = __builtin_amdgcn_readlane(nb, q);
+                    nbu = o > nbu ? o : nbu;
+                }
+                const uint32_t gm32 = G == 32 ? ~0u : (1u << (G & 31)) - 1u;
+                for (int b0 = 0; b0 < nbu; b0 += 2 * G) {
+                    double xa, ya, za, xb, yb, zb;
+                    load_bead<HBM>(P, min(b0 + t, N - 1), xa, ya, za);
+                    load_bead<HBM>(P, min(b0 + G + t, N - 1), xb, yb, zb);
+                    const uint64_t ua = __ballot(b0 + t < nb && !(tip_dist2(xa, ya, za) >= cull2)),
+                                   ub = __ballot(b0 + G + t < nb && !(tip_dist2(xb, yb, zb) >= cull2));
+                    if ((ua | ub) == 0) continue;
+                    // this group's flagged beads b0 + bit, two at a time
+                    uint64_t f = (uint64_t)((uint32_t)(ua >> gbase) & gm32) |
+                                 (uint64_t)((uint32_t)(ub >> gbase) & gm32) << G;
+                    while (__ballot(f != 0) != 0) {
+                        const bool one = f != 0;
+                        const int ja = one ? __builtin_ctzll(f) : 0;
+                        f &= f - (one ? 1 : 0);
+                        const bool two = f != 0;
+                        const int jb = two ? __builtin_ctzll(f) : ja;
+                        f &= f - (two ? 1 : 0);
+                        double px, py, pz, qx, qy, qz;
+                        load_bead<HBM>(P, b0 + ja, px, py, pz);
+                        load_bead<HBM>(P, b0 + jb, qx, qy, qz);
+                        const bool ha = overlaps(px, py, pz), hb = overlaps(qx, qy, qz);
+                        blocked = blocked | (one & (ha | hb));
+                    }
+                }
+            }
+
+            const bool fr = takes & !blocked;
+            const uint64_t gm = (__ballot(fr) >> (gbase + ph * kp)) & kmask;
+            const uint32_t m = (uint32_t)__popcll(gm);
+            const uint32_t x = half_word(sel, (uint32_t)e);
+            const uint32_t p = x * m;
+            uint32_t r = p >> 16;
+            if (__builtin_expect(act && (p & 0xFFFFu) < m, 0)) {
+                r = lemire_redraw16(a.seed, g, (uint32_t)i | hi, m, x);
+                if (r == kPickFailed) {
+                    rng_fail = true;
+                    r = 0;
+                }
+            }
+            const bool chosen = fr && (uint32_t)__popcll(gm & lower) == r;
+            const uint64_t cb = (__ballot(chosen) >> (gbase + ph * kp)) & kmask;
+            const int src = gbase + ph * kp + (cb ? __builtin_ctzll(cb) : 0);
+            double nx, ny, nz;
+            if constexpr (G == 64) {
+                const int usrc = __builtin_amdgcn_readfirstlane(src);
+                nx = lane_double(cx, usrc); ny = lane_double(cy, usrc); nz = lane_double(cz, usrc);
+            } else {
+                nx = __shfl(cx, src, 64); ny = __shfl(cy, src, 64); nz = __shfl(cz, src, 64);
+            }
+            if (chosen) {
+                double *o = P + 3 * i;
+                o[0] = cx; o[1] = cy; o[2] = cz;
+                if constexpr (HBM) {
+                    double *w = ring + 3 * (i & (kRing - 1));
+                    w[0] = cx; w[1] = cy; w[2] = cz;
+                }
+            }
+            const bool ok = act && m != 0u;
+            if (ok) {
+                x3 = x2; y3 = y2; z3 = z2;
+                x2 = tx; y2 = ty; z2 = tz;
+                tx = nx; ty = ny; tz = nz;
+                n_mine += (m == (uint32_t)t + 1u) ? 1u : 0u;
+                ++placed;
+            }
+            alive = alive && (ok || !act) && placed < N;
+            wave_sync();
+        }
+        i0 += 8;
+    }
+    if (rng_fail) atomicExch(a.status, 6);
+    publish_log_w_max(a, best);
+}
+
+template <int G>
+__global__ __launch_bounds__(64) void grow_real_queue(GrowArgs a)
+{
+    extern __shared__ double lds[];
+    grow_real_queue_body<G, false>(a, lds, nullptr);
+}
+
+// Batched launch: block b serves the ensemble whose block range holds b.
+template <int G>
+__global__ __launch_bounds__(64) void grow_real_queue_batch(const GrowEntry *tab, const uint64_t *block0, int n,
+                                                            uint64_t base)
+{
+    extern __shared__ double lds[];
+    const int e = find_segment(block0, n, base + blockIdx.x);
+    grow_real_queue_body<G, false>(tab[e].a, lds, nullptr);
+}
+
+// Chains beyond the LDS limit: block s grows its chains in HBM plane region s.
 __global__ __launch_bounds__(64) void grow_real_hbm(GrowArgs a)
 {
-    for (uint64_t bid = blockIdx.x; bid < a.n_chains; bid += gridDim.x)
-        grow_real_body<64, true>(a, bid, blockIdx.x);
+    __shared__ double ring[3 * kRing];
+    grow_real_queue_body<64, true>(a, a.bead_slots + (size_t)blockIdx.x * 3 * a.n_monomers, ring);
 }
 
 // Largest bead count of the LDS-resident kernel, and of the HBM one.  LDS
@@ -577,6 +962,25 @@ uint32_t real_hbm_slots(int n_monomers, uint64_t n_chains)
 {
     if (n_monomers <= kRealLdsMax) return 0;
     return (uint32_t)(n_chains < 2048 ? n_chains : 2048);
+}
+
+// Queued kernel with G lanes per chain, beads in LDS.
+static hipError_t queue_shape(int N, int G, GrowVariant *v)
+{
+    v->family = 5;
+    v->p0 = G;
+    v->p1 = 0;
+    v->p2 = 0;
+    v->threads = 64;
+    v->cpb = 64 / G;
+    v->shmem = (size_t)(64 / G) * queue_stride(N, G) * sizeof(double);
+    if (v->shmem > 163840) return hipErrorInvalidValue;
+    v->H = 0;
+    v->S = 0;
+    // blocks that fill the GPU: LDS, and 4 waves per SIMD (128 VGPRs)
+    const uint32_t per_cu = (uint32_t)(163840 / v->shmem);
+    v->max_blocks = 256u * (per_cu < 16u ? per_cu : 16u);
+    return hipSuccess;
 }
 
 // Shape of the LDS kernel for N beads, G lanes per chain (8..64, G >= k: one
@@ -602,6 +1006,26 @@ static hipError_t real_shape(int N, int k, int G, int threads, GrowVariant *v)
     return hipSuccess;
 }
 
+// Lanes of the queued kernel for a call, 0 where the lockstep kernel serves it.
+// Few trials and long chains meet dead ends early, which the lockstep kernel
+// pays for to the last step of its wave; and the queued kernel's skipped
+// blocks save more the longer the chain.  Kernel time, lockstep / queued (16,
+// 32, 64 lanes), MI355X, b = sigma = 1:
+//   k = 4:  N = 64 1.35 / 1.50 1.98 3.34 ms; N = 100 1.52 / 1.15 1.32 2.06;
+//           N = 160 3.77 / 1.67 1.57 2.25; N = 400 2.76 / 2.07 1.48 1.46
+//   k = 8:  N = 128 2.73 / 3.02 3.28 4.69; N = 144 3.77 / 3.68 3.68 5.19;
+//           N = 256 8.62 / 10.1 6.97 7.93; N = 300 7.15 / 7.51 4.88 4.58;
+//           N = 1000 4.51 / - 7.17 3.40
+//   k = 16: N = 300 2.94 / 4.68 3.28 2.93; N = 400 4.01 / 8.23 5.10 3.80
+//   k = 32: N = 256 1.27 / - 1.71 1.64; N = 500 2.41 / - 3.25 1.97
+//   k = 64: N = 256 0.98 / - - 1.13; N = 1000 2.49 / - - 2.37
+static int queue_lanes(int N, int k)
+{
+    if (k <= 4) return N < 80 ? 0 : (N < 140 ? 16 : (N < 400 ? 32 : 64));
+    if (k <= 8) return N < 144 ? 0 : (N < 280 ? 32 : 64);
+    return N < (k <= 16 ? 400 : (k <= 32 ? 500 : 1000)) ? 0 : 64;
+}
+
 // Built-in rule.  Lanes per chain: at least the next power of two >= k (one
 // trial per lane), and enough that the chains whose planes fit in a CU's LDS
 // still fill about 8 waves (G >= 0.075 N); the extra lanes share the culling
@@ -610,7 +1034,7 @@ static hipError_t real_shape(int N, int k, int G, int threads, GrowVariant *v)
 // blocks: four one-chain waves sharing a block's padded planes were measured
 // 1.2-2.3x slower for 432 <= N <= 672 (k = 8) than four one-wave blocks.  A
 // legal mapping of the tuning table replaces the rule.
-hipError_t real_variant(const GrowArgs &a, GrowVariant *v)
+hipError_t real_variant(const GrowArgs &a, GrowVariant *v, bool scan)
 {
     const int N = a.n_monomers;
     if (N > kRealLdsMax) {
@@ -630,6 +1054,10 @@ hipError_t real_variant(const GrowArgs &a, GrowVariant *v)
     if (tuned_mapping(1 /* hard spheres */, N, a.k_trials, &tl, &tt) &&
         real_shape(N, a.k_trials, tl, tt, v) == hipSuccess)
         return hipSuccess;
+    if (!scan) {
+        const int G = queue_lanes(N, a.k_trials);
+        if (G && queue_shape(N, G, v) == hipSuccess) return hipSuccess;
+    }
     int need = a.k_trials;
     const int occ = (3 * N + 39) / 40; // ceil(0.075 N)
     if (occ > need) need = occ;
@@ -682,11 +1110,40 @@ static hipError_t dispatch_real(const GrowArgs &a, const GrowVariant &v, const G
     }
 }
 
+template <int G>
+static hipError_t launch_queue(const GrowArgs &a, const GrowEntry *tab, const uint64_t *block0, int n,
+                               uint64_t blocks, size_t shmem, hipStream_t s)
+{
+    const void *fn = tab ? (const void *)grow_real_queue_batch<G> : (const void *)grow_real_queue<G>;
+    if (shmem > 65536) {
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+        if (e != hipSuccess) return e;
+    }
+    return launch_sliced(blocks, 64, [&](uint64_t b0, uint32_t nb) {
+        if (tab)
+            hipLaunchKernelGGL((grow_real_queue_batch<G>), dim3(nb), dim3(64), shmem, s, tab, block0, n, b0);
+        else
+            hipLaunchKernelGGL((grow_real_queue<G>), dim3(nb), dim3(64), shmem, s, a);
+    });
+}
+
+static hipError_t dispatch_queue(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab,
+                                 const uint64_t *block0, int n, uint64_t blocks, size_t shmem, hipStream_t s)
+{
+    switch (v.p0) {
+    case 16: return launch_queue<16>(a, tab, block0, n, blocks, shmem, s);
+    case 32: return launch_queue<32>(a, tab, block0, n, blocks, shmem, s);
+    default: return launch_queue<64>(a, tab, block0, n, blocks, shmem, s);
+    }
+}
+
 hipError_t launch_grow_real(const GrowArgs &a, hipStream_t s)
 {
     GrowVariant v;
-    hipError_t e = real_variant(a, &v);
+    hipError_t e = real_variant(a, &v, false);
     if (e != hipSuccess) return e;
+    if (v.family == 5)
+        return dispatch_queue(a, v, nullptr, nullptr, 0, variant_blocks(v, a.n_chains), v.shmem, s);
     if (v.p1) {
         if (!a.bead_slots || a.n_slots == 0) return hipErrorInvalidValue;
         hipLaunchKernelGGL(grow_real_hbm, dim3(a.n_slots), dim3(64), 0, s, a);
@@ -694,6 +1151,12 @@ hipError_t launch_grow_real(const GrowArgs &a, hipStream_t s)
     }
     const uint64_t blocks = (a.n_chains + v.cpb - 1) / v.cpb;
     return dispatch_real(a, v, nullptr, nullptr, 0, blocks, v.shmem, s);
+}
+
+hipError_t launch_real_queue_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
+                                   uint64_t blocks, size_t shmem, hipStream_t s)
+{
+    return dispatch_queue(GrowArgs{}, v, tab, block0, n, blocks, shmem, s);
 }
 
 hipError_t launch_real_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,

@@ -30,7 +30,9 @@ void lattice_reg_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v
 hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v, bool scan);
 hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                               int n, uint64_t blocks, size_t shmem, hipStream_t s);
-hipError_t real_variant(const GrowArgs &a, GrowVariant *v);
+hipError_t real_variant(const GrowArgs &a, GrowVariant *v, bool scan);
+hipError_t launch_real_queue_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
+                                   uint64_t blocks, size_t shmem, hipStream_t s);
 hipError_t launch_lattice_reg_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                                     int n, uint64_t blocks, hipStream_t s);
 hipError_t launch_lattice_lds_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
@@ -490,7 +492,7 @@ hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::Gr
     probe.n_chains = cfg->n_chains;
     probe.max_rounds = (cfg->flags & RSAW_RESTART) ? 65536u : 1u;
     const bool i16 = cfg->coord_type == RSAW_I16;
-    if (!L.lattice) return rsaw::real_variant(probe, v);
+    if (!L.lattice) return rsaw::real_variant(probe, v, scan);
     if (L.z26) return rsaw::lattice26_variant(probe, L.exact, i16, v);
     if (L.exact || cfg->n_monomers <= 64) {
         rsaw::lattice_reg_variant(probe, L.exact, i16, v);
@@ -540,6 +542,8 @@ rsaw_status run_batch(const BatchLaunch &B, hipStream_t s)
         else if (v.family == 1)
             e = rsaw::launch_lattice_lds_batch(v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks, G.shmem,
                                                s);
+        else if (v.family == 5)
+            e = rsaw::launch_real_queue_batch(v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks, G.shmem, s);
         else if (v.family == 4)
             e = rsaw::launch_lattice_set(rsaw::GrowArgs{}, v, B.d_gtab + G.first, B.d_gb0 + G.first, G.cnt, G.blocks,
                                          G.shmem, s);

@@ -235,7 +235,7 @@ inline hipError_t launch_sliced(uint64_t blocks, int threads, F &&launch_one)
 // template parameters and block size share one batched launch.
 struct GrowVariant {
     int family;         // 0 lattice (registers), 1 lattice (LDS), 2 hard spheres, 3 26-neighbour lattice,
-                        // 4 lattice (site set)
+                        // 4 lattice (site set), 5 hard spheres (queued)
     int p0, p1, p2;     // template parameters of the family
     int threads;        // threads per block
     int cpb;            // chains per block
