@@ -88,7 +88,8 @@ __device__ __forceinline__ uint32_t wide_pair(uint32_t wa, uint32_t wb, uint32_t
 
 // Byte words hold each coordinate plus 128 in one byte.  Up to N = 128 no
 // coordinate can leave [-127, 127].  Longer chains ("boxed" byte words)
-// stop growing a chain whose new tip reaches |coordinate| = E (127, or the
+// stop growing a chain whose new tip reaches |coordinate| = E (127 in LDS,
+// 120 in registers, where the tip is looked at every eight steps, or the
 // launch's byte_box when a caller lowers it), before the byte test and the
 // carry-free move could stop being exact at -128 and +128; the block then
 // grows that chain again from its first draw in wide words (the same draws
@@ -466,7 +467,13 @@ __device__ void regrow_wide(const GrowArgs &a, uint64_t first_chain, bool mine, 
 // 4 waves it spills in the step loop.
 // With the two-operation pair test of lattice_common.hpp (four operations in
 // the figures above): N = 256, 10^6 chains, 3.38 -> 2.68 ms; N = 2048, 10^5
-// chains, 25.2 -> 21.2 ms; the rest of a step is now the larger part.
+// chains, 25.2 -> 21.2 ms.  The rest of a step was then its larger part: with
+// Philox blocks drawn by one lane each and handed round the group, n_m
+// counted by one lane each, no selects for dead chains (their masks are
+// empty) and the box looked at every eight steps, N = 80, 0.437 -> 0.380 ms;
+// N = 256, 2.69 -> 2.08 ms; N = 512, 3 10^5 chains, 3.29 -> 2.45 ms; N = 2048,
+// 21.2 -> 16.9 ms.  At 2 waves per SIMD, without the spills (41 registers,
+// outside the pair tests), N = 256 takes 2.76 ms.
 constexpr int kGrpSlots = 32; // slots per lane and plane
 
 template <int G, typename CT>
@@ -474,10 +481,13 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
 {
     constexpr int SL = kGrpSlots;
     const int t = threadIdx.x & (G - 1);
+    const int gbase = threadIdx.x & 63 & ~(G - 1);
     const uint64_t g = a.chain_offset + c;
     const int N = a.n_monomers;
+    // Box of the byte words: |coordinate| is looked at every eight steps, so
+    // the edge lies eight below the last exact one.
     const bool boxed = N > kByteExactN;
-    const int edge = a.byte_box > 0 ? a.byte_box : 127; // box of the byte words
+    const int edge = a.byte_box > 0 && a.byte_box < 120 ? a.byte_box : 120;
 
     uint32_t pe[SL], po[SL]; // planes of even and odd monomers
 #pragma unroll
@@ -486,9 +496,11 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
     bool alive = false;
     bool left_box = false;
     int grown = 1;
-    uint64_t cnt = 0; // n_m in 12-bit fields at 12 (m - 1), m = 1..6
+    // steps with m free candidates: lane t counts m = t + 2 (m = 1 and the one
+    // m = 6 of step 1 need no count); with two lanes also m = t + 4
+    uint32_t n_mine = 0, n_mine2 = 0;
     bool rng_fail = false;
-    Philox4 blk{0, 0, 0, 0};
+    Philox4 mine{0, 0, 0, 0}; // this lane's block of the next G
     double res_lw = -__builtin_huge_val();
     int64_t res_nn = 0;
     int32_t res_ex = 0, res_ey = 0, res_ez = 0;
@@ -505,16 +517,15 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
                 po[s] = pending ? 0u : po[s];
             }
         }
-        if (pending) {
-            ta = kByteOrigin;
-            cnt = 0;
-        }
+        if (pending) ta = kByteOrigin;
+        n_mine = 0;
+        n_mine2 = 0;
         pe[0] = (pending && t == 0) ? byte_history(kByteOrigin) : pe[0];
-        alive = pending;
+        uint32_t live = pending ? ~0u : 0u; // zero after a dead end or outside the box
         grown = 1;
         const uint32_t hi = rd << 16;
 
-        const auto step = [&](int i, uint32_t(&pl)[SL]) {
+        const auto step = [&](int i, uint32_t x, uint32_t(&pl)[SL]) {
             const int ns = ((i >> 1) + G - 1) / G; // slots holding entries of plane i mod 2
             const uint32_t tref = ta & kByteCoords;
             uint32_t occ = 0, occ2 = 0;
@@ -529,52 +540,69 @@ __device__ __forceinline__ bool lattice_grp_grow(const GrowArgs &a, const uint32
             }
             occ |= occ2;
             occ = group_or<G>(occ);
-            const uint32_t freem = byte_free(occ, ta, ~0u);
+            const uint32_t freem = byte_free(occ, ta, live);
             const uint32_t m = __builtin_popcount(freem);
-
-            if (i == 1 || (i & 7) == 0) blk = draw(a.seed, g, (uint32_t)(i >> 3) | hi, kSlotSelect, 0);
-            const uint32_t x = half_word(blk, (uint32_t)(i & 7));
             const uint32_t p = x * m;
             uint32_t r = p >> 16;
-            if (__builtin_expect(alive && (p & 0xFFFFu) < m, 0)) {
+            if (__builtin_expect((p & 0xFFFFu) < m, 0)) { // never for m = 0
                 r = lemire_redraw16(a.seed, g, (uint32_t)i | hi, m, x);
                 if (r == kPickFailed) {
                     rng_fail = true;
                     r = 0;
                 }
             }
-
-            bool step_ok = alive && m != 0;
-            const uint32_t na = ta + lut[(freem << 2) | r];
-            if (boxed && i >= edge) {
-                const bool out = byte_out(na, edge);
-                left_box = left_box || (step_ok && out);
-                alive = alive && !(step_ok && out);
-                step_ok = step_ok && !out;
-            }
-            grown = (alive && m == 0) ? i : grown;
-            alive = alive && m != 0;
-            ta = step_ok ? na : ta;
-            cnt += step_ok ? (1ull << (12u * (m - 1u))) : 0ull;
+            ta += lut[(freem << 2) | r]; // 0 for an empty mask: a dead chain stays
+            const bool ok = m != 0u;
+            live = ok ? live : 0u;
+            grown += ok ? 1 : 0;
+            n_mine += m == (uint32_t)t + 2u ? 1u : 0u;
+            if constexpr (G == 2) n_mine2 += m == (uint32_t)t + 4u ? 1u : 0u;
             const int k = i >> 1;
             const uint32_t old = pl[k / G];
-            pl[k / G] = (step_ok && t == (k & (G - 1))) ? byte_history(na) : old;
+            pl[k / G] = (ok && t == (k & (G - 1))) ? byte_history(ta) : old;
         };
-        for (int i = 1; i < N; i += 2) {
-            step(i, po);
-            if (i + 1 < N) step(i + 1, pe);
+        for (int i0 = 0; i0 < N; i0 += 8) {
+            // one Philox block serves eight steps; the lanes draw G blocks at a
+            // time and hand them round
+            const int q = i0 >> 3;
+            if ((q & (G - 1)) == 0) mine = draw(a.seed, g, (uint32_t)(q + t) | hi, kSlotSelect, 0);
+            const int from = 4 * (gbase + (q & (G - 1)));
+            uint32_t w[4] = {mine.x0, mine.x1, mine.x2, mine.x3};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)w[j]);
+#pragma unroll 1
+            for (int i = i0; i < i0 + 8 && i < N; i += 2) {
+                if (i > 0) step(i, w[0] & 0xFFFFu, pe);
+                if (i + 1 < N) step(i + 1, w[0] >> 16, po);
+                w[0] = w[1];
+                w[1] = w[2];
+                w[2] = w[3];
+            }
+            if (boxed && i0 + 7 >= edge && live != 0u && byte_out(ta, edge)) {
+                left_box = true;
+                live = 0u;
+            }
             // one chain per wave: the wave leaves once its chain has ended
             if constexpr (G == 64) {
-                if (__ballot(alive) == 0) break;
+                if (__ballot(live != 0u) == 0) break;
             }
         }
-        if (alive) grown = N;
+        alive = live != 0u;
         double lw = 0.0;
         if (N >= 2) {
-            lw = lw + (double)(uint32_t)((cnt >> 12) & 0xFFFu) * a.logm[2];
-            lw = lw + (double)(uint32_t)((cnt >> 24) & 0xFFFu) * a.logm[3];
-            lw = lw + (double)(uint32_t)((cnt >> 36) & 0xFFFu) * a.logm[4];
-            lw = lw + (double)(uint32_t)((cnt >> 48) & 0xFFFu) * a.logm[5];
+            const uint32_t n2 = __shfl(n_mine, gbase, 64), n3 = __shfl(n_mine, gbase + 1, 64);
+            uint32_t n4, n5;
+            if constexpr (G == 2) {
+                n4 = __shfl(n_mine2, gbase, 64);
+                n5 = __shfl(n_mine2, gbase + 1, 64);
+            } else {
+                n4 = __shfl(n_mine, gbase + 2, 64);
+                n5 = __shfl(n_mine, gbase + 3, 64);
+            }
+            lw = lw + (double)n2 * a.logm[2];
+            lw = lw + (double)n3 * a.logm[3];
+            lw = lw + (double)n4 * a.logm[4];
+            lw = lw + (double)n5 * a.logm[5];
             lw = lw + a.logm[6];
         }
 
@@ -795,18 +823,18 @@ hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const Gro
 // Calls that the site set serves instead of the scanning kernels of this
 // file (unless the tuning table maps the call to one of them).  Its step
 // costs the same at every length, a scan's grows with it; its step also takes
-// about 1.2 times as long when few waves run.  MI355X, kernel time, set
-// against scan: 5 10^5 chains, N = 400, 4.03 / 4.02 ms; N = 512, 5.63 / 5.46;
-// 3 10^5 chains, N = 513, 4.09 / 5.78; N = 640, 4.95 / 7.48; 10^5 chains,
-// N = 2048, 10.8 / 21.2; 5000 chains, N = 10000, 7.1 / 81.  2000 chains:
-// N = 600, 0.29 / 0.23; N = 1000, 0.444 / 0.436; N = 2000, 0.81 / 0.91.
+// longer than a scan's over few slots when few waves run.  MI355X, kernel
+// time, set against scan: N = 640, 3 10^5 chains, 4.97 / 5.17 ms; N = 1000,
+// 2 10^5, 6.39 / 6.18; N = 1025, 2 10^5, 6.57 / 10.6; N = 2048, 10^5, 10.9 /
+// 16.9, 5000 chains, 0.95 / 3.02; N = 2000, 2000 chains, 0.82 / 0.67;
+// N = 3000, 2000 chains, 1.17 / 4.91; N = 5000, 300 chains, 1.70 / 3.64.
 // Restarts, which the scan's waves repeat for every chain of the wave, 10^5
-// chains: N = 300, 1.61 / 1.18; N = 500, 1.99 / 2.70; N = 600, 2.30 / 5.12.
+// chains: N = 512, 2.05 / 2.06; N = 513, 2.07 / 2.76; N = 600, 2.26 / 3.53;
+// 5000 chains: N = 600, 0.69 / 0.70.
 static bool use_site_set(const GrowArgs &a)
 {
     const int N = a.n_monomers;
-    if (N > 1024) return true;
-    return a.n_chains >= 16384 && (N > 512 || (a.max_rounds > 1 && N > 400));
+    return N > 2048 || (N > 1024 && a.n_chains >= 4096) || (N > 512 && a.max_rounds > 1);
 }
 
 // Variant for 64 < N <= 16384; with `scan`, a scanning kernel's.  Built-in rule (measured on MI355X, 10^4 to

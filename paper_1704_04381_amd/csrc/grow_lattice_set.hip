@@ -42,12 +42,11 @@
 // Sums over the placed monomers come from the bitmaps when a chain ends, in
 // the pass that clears the table for the next one.
 //
-// Bound, from N = 1000 on, by the latency of a step (about 750 cycles: one
-// dependent LDS read, 40 % of it, and 62 vector instructions) at the number
-// of chains whose tables fit in a CU's LDS; below, by VALU issue (0.86 of it
-// at N = 512).  MI355X, whole calls, scan of the history (grow_lattice_lds.hip)
-// -> set: N = 2048, 10^5 chains, 21.3 -> 10.9 ms; N = 10000, 5000 chains,
-// 81.9 -> 7.4 ms, where the longest chain's 10^4 steps alone take 3 ms.
+// Bound by the latency of a step (about 750 cycles: one dependent LDS read,
+// 40 % of it, and 62 vector instructions) at the number of chains whose tables
+// fit in a CU's LDS.  MI355X, whole calls, scan of the history with 64 lanes or
+// in LDS -> set: N = 2048, 10^5 chains, 16.9 -> 10.9 ms; N = 10000, 5000
+// chains, 81.9 -> 7.4 ms, where the longest chain's 10^4 steps alone take 3 ms.
 #include "lattice_common.hpp"
 
 #include <type_traits>

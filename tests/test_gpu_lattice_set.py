@@ -25,14 +25,14 @@ def _restore():
 
 
 @pytest.mark.parametrize("N,M,seed,coord,edge,offset,restart", [
-    (1_025, 1, 201, "i32", 0, 0, False),
+    (2_049, 1, 201, "i32", 0, 0, False),
     (1_025, 700, 202, "i16", 0, 0, True),
-    (2_048, 150, 203, "i32", 0, (1 << 32) + 11, False),
-    (513, 16_384, 204, "i16", 0, 0, False),   # the rule's smallest ensemble
-    (401, 16_390, 205, "i32", 0, 0, True),    # its shortest chains
+    (2_100, 150, 203, "i32", 0, (1 << 32) + 11, False),
+    (1_025, 4_096, 204, "i16", 0, 0, False),  # the rule's smallest ensemble
+    (513, 1_500, 205, "i32", 0, 0, True),     # its shortest chains
     (5_000, 25, 206, "i16", 0, 0, False),     # two chains per wave
     (16_384, 5, 207, "i32", 0, 0, False),     # one chain per wave, the longest
-    (1_100, 90, 208, "i32", 30, 0, False),    # some chains without the set
+    (2_060, 90, 208, "i32", 40, 0, False),    # some chains without the set
     (1_030, 40, 209, "i16", 1, 7, True),      # all of them
 ])
 def test_site_set_bit_exact(N, M, seed, coord, edge, offset, restart):
@@ -41,7 +41,7 @@ def test_site_set_bit_exact(N, M, seed, coord, edge, offset, restart):
 
 
 def test_site_set_in_a_batch():
-    specs = [dict(geometry="lattice", N=1_200, k=6, n_chains=60, seed=211),
+    specs = [dict(geometry="lattice", N=2_200, k=6, n_chains=60, seed=211),
              dict(geometry="lattice", N=3_000, k=6, n_chains=20, seed=212, coord="i16"),
              dict(geometry="lattice", N=1_026, k=6, n_chains=130, seed=213, restart=True),
              dict(geometry="lattice", N=300, k=6, n_chains=100, seed=214)]
