@@ -48,6 +48,73 @@ __device__ __forceinline__ void add_into(ThreadSums &a, const ThreadSums &b)
     a.ex[2] += b.ex[2];
 }
 
+constexpr int kFields = kNumSums + 2 + 6;    // ThreadSums as 64-bit fields
+constexpr size_t kTreeBytes = (size_t)kFields * (kRT / 2) * sizeof(uint64_t);
+
+// The block's sum of its threads' sums in thread 0, by the fixed tree
+// s[t] += s[t + 128], ..., s[t + 1]: the two steps across waves through LDS,
+// one array per field (a thread's 128 bytes side by side met 32-way bank
+// conflicts, and eight steps eight barriers), the six within a wave by
+// shuffles.  The exact sums ride along only where the call has them.  10^5
+// chains, N = 16: 12.6 -> 5.4 us for the partials, 8.3 -> 5.7 us for the final
+// kernel.  Every thread of the block calls this.
+__device__ __forceinline__ void block_sum(ThreadSums &my, bool exact, uint64_t *sm)
+{
+    const int tid = threadIdx.x;
+    const auto put = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < kNumSums; ++q) sm[q * (kRT / 2) + i] = (uint64_t)__double_as_longlong(my.s[q]);
+        sm[kNumSums * (kRT / 2) + i] = my.alive;
+        sm[(kNumSums + 1) * (kRT / 2) + i] = my.steps;
+        if (exact) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                sm[(kNumSums + 2 + 2 * q) * (kRT / 2) + i] = (uint64_t)my.ex[q];
+                sm[(kNumSums + 3 + 2 * q) * (kRT / 2) + i] = (uint64_t)(my.ex[q] >> 64);
+            }
+        }
+    };
+    const auto take = [&](int i) {
+        ThreadSums o;
+#pragma unroll
+        for (int q = 0; q < kNumSums; ++q) o.s[q] = __longlong_as_double((long long)sm[q * (kRT / 2) + i]);
+        o.alive = sm[kNumSums * (kRT / 2) + i];
+        o.steps = sm[(kNumSums + 1) * (kRT / 2) + i];
+        o.ex[0] = o.ex[1] = o.ex[2] = 0;
+        if (exact) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                o.ex[q] = ((unsigned __int128)sm[(kNumSums + 3 + 2 * q) * (kRT / 2) + i] << 64) |
+                          sm[(kNumSums + 2 + 2 * q) * (kRT / 2) + i];
+        }
+        add_into(my, o);
+    };
+    if (tid >= 128) put(tid - 128);
+    __syncthreads();
+    if (tid < 128) take(tid);
+    __syncthreads();
+    if (tid >= 64 && tid < 128) put(tid - 64);
+    __syncthreads();
+    if (tid >= 64) return;
+    take(tid);
+#pragma unroll 1
+    for (int off = 32; off > 0; off >>= 1) {
+        ThreadSums o;
+#pragma unroll
+        for (int q = 0; q < kNumSums; ++q) o.s[q] = __shfl_down(my.s[q], off, 64);
+        o.alive = __shfl_down(my.alive, off, 64);
+        o.steps = __shfl_down(my.steps, off, 64);
+        o.ex[0] = o.ex[1] = o.ex[2] = 0;
+        if (exact) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                o.ex[q] = ((unsigned __int128)__shfl_down((uint64_t)(my.ex[q] >> 64), off, 64) << 64) |
+                          __shfl_down((uint64_t)my.ex[q], off, 64);
+        }
+        add_into(my, o);
+    }
+}
+
 // Histogram weights are accumulated as fixed-point integers: w in [0, 1] is
 // split into three 32-bit limbs (w = l0 2^-32 + l1 2^-64 + l2 2^-96 + t with
 // 0 <= t < 2^-96; each step of the split is exact in binary64).  Integer
@@ -70,8 +137,7 @@ __device__ __forceinline__ void split_limbs(double w, uint64_t &l0, uint64_t &l1
 __device__ __forceinline__ void reduce_partials_body(const ReduceArgs &a, uint64_t bid)
 {
     extern __shared__ unsigned char smem[];
-    ThreadSums *ts = (ThreadSums *)smem;                                   // [kRT]
-    unsigned long long *hacc = (unsigned long long *)(smem + sizeof(ThreadSums) * kRT); // [4][bins]
+    unsigned long long *hacc = (unsigned long long *)(smem + kTreeBytes); // [4][bins]
     const int tid = threadIdx.x;
     for (int q = tid; q < 4 * a.bins; q += kRT) hacc[q] = 0ull;
     __syncthreads();
@@ -87,55 +153,69 @@ __device__ __forceinline__ void reduce_partials_body(const ReduceArgs &a, uint64
     for (int q = 0; q < kNumSums; ++q) my.s[q] = 0.0;
     my.alive = 0; my.steps = 0; my.ex[0] = 0; my.ex[1] = 0; my.ex[2] = 0;
 
-    for (uint64_t q = begin + tid; q < end; q += kRT) {
-        const double lw = a.log_w[q];
-        my.steps += (uint64_t)a.n_grown[q] - 1u;
-        if (!(lw > -__builtin_huge_val())) continue;
-        const double w = exp(lw - L);
-        const double A = a.r2[q];
-        const double G = a.rg2[q];
-        const double ww = w * w;
-        my.alive += 1;
-        my.s[0] = my.s[0] + w;
-        my.s[1] = my.s[1] + ww;
-        my.s[2] = my.s[2] + w * A;
-        my.s[3] = my.s[3] + ww * A;
-        my.s[4] = my.s[4] + ww * A * A;
-        my.s[5] = my.s[5] + w * G;
-        my.s[6] = my.s[6] + ww * G;
-        my.s[7] = my.s[7] + ww * G * G;
-        if (a.exact) {
-            const unsigned __int128 W = a.w_exact[q];
-            my.ex[0] += W;
-            my.ex[1] += W * (unsigned __int128)(uint64_t)A;
-            my.ex[2] += W * (unsigned __int128)(uint64_t)a.n2rg2[q];
+    // kUnroll chains of a thread at a time, their loads in flight together (one
+    // at a time waited for memory at every chain: 10^7 chains, 256 bins,
+    // 97.8 -> 65.5 us); summed in index order as before
+    constexpr int kUnroll = 4;
+    for (uint64_t q0 = begin + tid; q0 < end; q0 += (uint64_t)kRT * kUnroll) {
+        double lws[kUnroll], r2s[kUnroll], rg2s[kUnroll];
+        uint16_t ngs[kUnroll];
+#pragma unroll
+        for (int j = 0; j < kUnroll; ++j) {
+            const uint64_t q = q0 + (uint64_t)kRT * j < end ? q0 + (uint64_t)kRT * j : q0;
+            lws[j] = a.log_w[q];
+            r2s[j] = a.r2[q];
+            rg2s[j] = a.rg2[q];
+            ngs[j] = a.n_grown[q];
         }
-        if (a.bins > 0) {
-            const double fb = floor((A * (double)a.bins) / nsq1);
-            const int bin = fb < 0.0 ? 0 : (fb >= (double)a.bins ? a.bins - 1 : (int)fb);
-            uint64_t l0, l1, l2;
-            split_limbs(w, l0, l1, l2);
-            atomicAdd(&hacc[bin], (unsigned long long)l0);
-            atomicAdd(&hacc[a.bins + bin], (unsigned long long)l1);
-            atomicAdd(&hacc[2 * a.bins + bin], (unsigned long long)l2);
-            atomicAdd(&hacc[3 * a.bins + bin], 1ull);
+#pragma unroll
+        for (int j = 0; j < kUnroll; ++j) {
+            const uint64_t q = q0 + (uint64_t)kRT * j;
+            if (q >= end) break;
+            const double lw = lws[j];
+            my.steps += (uint64_t)ngs[j] - 1u;
+            if (!(lw > -__builtin_huge_val())) continue;
+            const double w = exp(lw - L);
+            const double A = r2s[j];
+            const double G = rg2s[j];
+            const double ww = w * w;
+            my.alive += 1;
+            my.s[0] = my.s[0] + w;
+            my.s[1] = my.s[1] + ww;
+            my.s[2] = my.s[2] + w * A;
+            my.s[3] = my.s[3] + ww * A;
+            my.s[4] = my.s[4] + ww * A * A;
+            my.s[5] = my.s[5] + w * G;
+            my.s[6] = my.s[6] + ww * G;
+            my.s[7] = my.s[7] + ww * G * G;
+            if (a.exact) {
+                const unsigned __int128 W = a.w_exact[q];
+                my.ex[0] += W;
+                my.ex[1] += W * (unsigned __int128)(uint64_t)A;
+                my.ex[2] += W * (unsigned __int128)(uint64_t)a.n2rg2[q];
+            }
+            if (a.bins > 0) {
+                const double fb = floor((A * (double)a.bins) / nsq1);
+                const int bin = fb < 0.0 ? 0 : (fb >= (double)a.bins ? a.bins - 1 : (int)fb);
+                uint64_t l0, l1, l2;
+                split_limbs(w, l0, l1, l2);
+                atomicAdd(&hacc[bin], (unsigned long long)l0);
+                atomicAdd(&hacc[a.bins + bin], (unsigned long long)l1);
+                atomicAdd(&hacc[2 * a.bins + bin], (unsigned long long)l2);
+                atomicAdd(&hacc[3 * a.bins + bin], 1ull);
+            }
         }
     }
 
-    ts[tid] = my;
-    __syncthreads();
-    for (int stride = kRT / 2; stride > 0; stride >>= 1) {
-        if (tid < stride) add_into(ts[tid], ts[tid + stride]);
-        __syncthreads();
-    }
+    block_sum(my, a.exact != 0, (uint64_t *)smem);
     if (tid == 0) {
         BlockPartial &bp = a.partials[bid];
-        for (int q = 0; q < kNumSums; ++q) bp.s[q] = ts[0].s[q];
-        bp.alive = ts[0].alive;
-        bp.steps = ts[0].steps;
+        for (int q = 0; q < kNumSums; ++q) bp.s[q] = my.s[q];
+        bp.alive = my.alive;
+        bp.steps = my.steps;
         for (int q = 0; q < 3; ++q) {
-            bp.ex[2 * q] = (uint64_t)ts[0].ex[q];
-            bp.ex[2 * q + 1] = (uint64_t)(ts[0].ex[q] >> 64);
+            bp.ex[2 * q] = (uint64_t)my.ex[q];
+            bp.ex[2 * q + 1] = (uint64_t)(my.ex[q] >> 64);
         }
     }
     for (int q = tid; q < 4 * a.bins; q += kRT) {
@@ -152,7 +232,7 @@ __global__ __launch_bounds__(kRT) void reduce_partials(ReduceArgs a)
 __device__ __forceinline__ void reduce_final_body(const ReduceArgs &a, uint32_t n_blocks, rsaw_summary *out,
                                                   double *hist_w, uint64_t *hist_n)
 {
-    __shared__ ThreadSums ts[kRT];
+    __shared__ uint64_t tree[kTreeBytes / sizeof(uint64_t)];
     const int tid = threadIdx.x;
     ThreadSums my;
 #pragma unroll
@@ -168,14 +248,9 @@ __device__ __forceinline__ void reduce_final_body(const ReduceArgs &a, uint32_t 
             o.ex[q] = ((unsigned __int128)bp.ex[2 * q + 1] << 64) | bp.ex[2 * q];
         add_into(my, o);
     }
-    ts[tid] = my;
-    __syncthreads();
-    for (int stride = kRT / 2; stride > 0; stride >>= 1) {
-        if (tid < stride) add_into(ts[tid], ts[tid + stride]);
-        __syncthreads();
-    }
+    block_sum(my, a.exact != 0, tree);
     if (tid == 0) {
-        const ThreadSums &t = ts[0];
+        const ThreadSums &t = my;
         const double M = (double)a.n_chains;
         const double S0 = t.s[0], S2 = t.s[1];
         const bool any = t.alive > 0;
@@ -251,7 +326,7 @@ __global__ __launch_bounds__(kRT) void reduce_final_batch(const ReduceEntry *tab
 
 size_t reduce_partials_shmem(int bins)
 {
-    return sizeof(ThreadSums) * kRT + (size_t)4 * bins * sizeof(unsigned long long);
+    return kTreeBytes + (size_t)4 * bins * sizeof(unsigned long long);
 }
 
 hipError_t launch_reduce(const ReduceArgs &a, uint32_t n_blocks, rsaw_summary *out,
