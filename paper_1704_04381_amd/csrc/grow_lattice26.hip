@@ -884,62 +884,56 @@ grow_lattice26_grp_batch(const GrowEntry *tab, const uint64_t *block0, int n, ui
     grow_lattice26_grp_body<G, CT, FMT>(tab[e].a, bid - block0[e], tab[e].S);
 }
 
-// Short chains (N <= 64): one lane per chain.  The lane's history sits in
-// LDS as one word per monomer, bytes (x + 64, y + 64, z + 64) plus 128 each
-// (coordinates stay within +-63), four monomers to a 16-byte group; group g
-// of lane L is entry g * T + L of the block's group array, so a wave reads
-// 1 KB of consecutive groups per ds_read_b128.  Unplaced entries hold the
-// sentinel 0x00808080 (raw coordinates -64, at least 2 from every tip).
-// Pair test of a stored word w against the tip word t (raw, unbiased), with
-// tp = t + 0x7F7F7F (z26_bits8):
-//   v    = w - tp                    bytes d + 1 when every |d| <= 1
-//   bad  = (v | (v + 0x010101)) & 0xFCFCFC   0 iff every |d| <= 1
-//   code = dot4(v, (1, 3, 9, 0));    occ |= sat(1 - bad) << code
-// six operations.  The counts n_m of the
-// steps with m free candidates are 8-bit fields in LDS (seven words per
-// lane); the r-th free code comes from the byte holding it and a 2 KB table
-// of the k-th set bit of every byte value.
+// Short chains (N <= 64): one lane per chain, the history in the lane's
+// registers, one word per monomer, bytes (x + 64, y + 64, z + 64) plus 128
+// each (coordinates stay within +-63).  A step tests the slots of monomers
+// 0 .. i - 2, four at a time behind one wave-uniform count test, two in a last
+// group with one or two left (a slot past them holds the tip, code 13, masked,
+// or the sentinel 0x00808080, raw coordinates -64, at least 2 from every tip),
+// six operations each (z26_bits8), and appends the new word with one indexed
+// register write.  The counts n_m of the steps with m free candidates are
+// 8-bit fields in LDS (seven words per lane); the r-th free code comes from
+// the byte holding it and a 2 KB table of the k-th set bit of every byte
+// value.  Coordinate sums run along with the steps.
+//
+// Bound by VALU issue.  Against the history in LDS (64 KB per 256-thread block:
+// 2 waves per SIMD, a b128 read per four tests; here 4 waves), MI355X, N = 64,
+// 10^7 chains, whole call: 5.43 -> 3.94 ms; N = 16, 1.95 -> 0.72 ms.
 constexpr int kZ26LaneMax = 64;
 constexpr int kZ26LaneThreads = 256;
 
-__host__ __device__ constexpr size_t z26_lane_shmem(int N, int T)
+__host__ __device__ constexpr size_t z26_lane_shmem(int T)
 {
-    return (size_t)((N + 3) / 4) * T * 16 + (size_t)7 * T * 4 + 32 * 4 + 2048;
+    return (size_t)7 * T * 4 + 32 * 4 + 2048;
 }
-
 
 template <bool EXACT, typename CT>
 __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint64_t bid)
 {
     constexpr int T = kZ26LaneThreads;
+    constexpr int HS = kZ26LaneMax / 2;
     const int N = a.n_monomers;
-    const int NQ = (N + 3) >> 2;
-    extern __shared__ uint4 z26l_lds[];
-    uint4 *groups = z26l_lds;                                   // [NQ][T]
-    uint32_t *hist = (uint32_t *)(groups + (size_t)NQ * T);     // [7][T]
+    extern __shared__ uint32_t z26l_lds[];
+    uint32_t *hist = z26l_lds;                                  // [7][T]
     uint32_t *lut = hist + 7 * T;                               // [32]
     uint8_t *sel = (uint8_t *)(lut + 32);                       // [256][8]
     __shared__ double logm[27];
     for (int q = threadIdx.x; q < 27; q += T) {
         const int dx = q % 3, dy = (q / 3) % 3, dz = q / 9; // each + 1
-        lut[q] = (uint32_t)(dx | dy << 8 | dz << 16);
+        lut[q] = (uint32_t)(dx | dy << 8 | dz << 16) - 0x00010101u;
         logm[q] = a.logm[q];
     }
     z26_fill_select_table(sel);
-    const uint4 sent = {kZ26Bias, kZ26Bias, kZ26Bias, kZ26Bias};
-    for (int q = threadIdx.x; q < NQ * T; q += T) groups[q] = sent;
     __syncthreads();
 
     const int L = threadIdx.x;
     const uint64_t c = bid * T + L;
     const bool valid = c < a.n_chains;
     const uint64_t g = a.chain_offset + c;
-    uint32_t *words = (uint32_t *)groups;
-    auto slot = [&](int j) -> uint32_t & { return words[(((size_t)(j >> 2) * T + L) << 2) + (j & 3)]; };
 
-    uint32_t tip = kZ26LaneOrigin;
-    bool alive = false;
-    int grown = 1;
+    uint32_t pl[HS], ph[HS]; // monomers 0-31 and 32-63
+#pragma unroll
+    for (int q = 0; q < HS; ++q) pl[q] = ph[q] = kZ26Bias;
     uint64_t wx = 1;
     bool rng_fail = false;
     Philox4 blk{0, 0, 0, 0};
@@ -952,38 +946,37 @@ __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint
     bool pending = valid;
 
     for (uint32_t rd = 0; rd < a.max_rounds; ++rd) {
-        if (pending) {
-            if (rd > 0)
-                for (int q = 0; q < NQ; ++q) groups[(size_t)q * T + L] = sent;
-            for (int q = 0; q < 7; ++q) hist[q * T + L] = 0u;
-            tip = kZ26LaneOrigin;
-            slot(0) = tip + kZ26Bias;
-            wx = 1;
+        if (rd > 0) {
+#pragma unroll
+            for (int q = 0; q < HS; ++q) pl[q] = ph[q] = kZ26Bias;
         }
-        alive = pending;
-        grown = 1;
+        for (int q = 0; q < 7; ++q) hist[q * T + L] = 0u;
+        uint32_t tip = kZ26LaneOrigin;
+        pl[0] = tip + kZ26Bias;
+        wx = 1;
+        bool alive = pending;
+        int grown = 1;
+        // raw coordinate sums over the monomers (x and z as 16-bit halves); a
+        // dead chain adds its tip again, taken out below
+        uint32_t sxz = 0x00400040u, sy = 0x00004000u, s2 = 3u * 64u * 64u;
         const uint32_t hi = rd << 16;
 
         for (int i = 1; i < N; ++i) {
-            // monomers 0 .. i-2 in groups of four; the last group may also hold
-            // the tip (code 13, masked) and sentinels
-            const int ng = (i + 2) >> 2;
+            const int ns = i - 1; // slots of monomers 0 .. i - 2
             const uint32_t tp = tip + 0x7F7F7Fu;
             uint32_t occ = 0, occ2 = 0;
-            auto test4 = [&](const uint4 &w) {
-                occ |= z26_bits8(w.x, tp);
-                occ2 |= z26_bits8(w.y, tp);
-                occ |= z26_bits8(w.z, tp);
-                occ2 |= z26_bits8(w.w, tp);
+            const auto test2 = [&](uint32_t w0, uint32_t w1) {
+                occ |= z26_bits8(w0, tp);
+                occ2 |= z26_bits8(w1, tp);
             };
-            int q = 0;
-            for (; q + 1 < ng; q += 2) { // two groups in flight, as in the group kernel
-                const uint4 w1 = groups[(size_t)q * T + L];
-                const uint4 w2 = groups[(size_t)(q + 1) * T + L];
-                test4(w1);
-                test4(w2);
+            const auto word = [&](int sl) { return sl < HS ? pl[sl] : ph[sl - HS]; };
+#pragma unroll
+            for (int q = 0; q < kZ26LaneMax / 4; ++q) {
+                if (4 * q >= ns) break;
+                test2(word(4 * q), word(4 * q + 1));
+                if (4 * q + 2 >= ns) break; // a tail of one or two slots
+                test2(word(4 * q + 2), word(4 * q + 3));
             }
-            if (q < ng) test4(groups[(size_t)q * T + L]);
             const uint32_t freem = ~(occ | occ2) & kZ26Codes;
             const uint32_t m = __builtin_popcount(freem);
 
@@ -998,19 +991,19 @@ __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint
                     r = 0;
                 }
             }
-            if (alive && m == 0) {
-                alive = false;
-                grown = i;
-            }
+            alive = alive && m != 0;
             if (alive) {
-                const uint32_t code = z26_select(freem, r, sel);
-                tip = tip + lut[code] - 0x00010101u;
-                slot(i) = tip + kZ26Bias;
+                tip = tip + lut[z26_select(freem, r, sel)];
                 atomicAdd(&hist[(m >> 2) * T + L], 1u << ((m & 3u) * 8u));
+                ++grown;
                 if (EXACT) wx = wx * (uint64_t)m;
             }
+            sxz += tip & 0x00FF00FFu;
+            sy += tip & 0x0000FF00u;
+            s2 = __builtin_amdgcn_udot4(tip, tip, s2, false);
+            if (i < HS) pl[i] = tip + kZ26Bias;
+            else ph[i - HS] = tip + kZ26Bias;
         }
-        if (alive) grown = N;
 
         if (pending && (alive || rd + 1 >= a.max_rounds)) {
             // log W = sum over m = 1..26, ascending, of n_m log m
@@ -1020,22 +1013,18 @@ __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint
                 const uint32_t nm = (hist[(mm >> 2) * T + L] >> ((mm & 3) * 8)) & 0xFFu;
                 lw = lw + (double)nm * logm[mm];
             }
-            int32_t sx = 0, sy = 0, sz = 0, s2 = 0;
-            for (int j = 0; j < grown; ++j) {
-                const uint32_t w = slot(j) - kZ26Bias;
-                const int32_t xx = (int32_t)(w & 0xFFu) - 64;
-                const int32_t yy = (int32_t)((w >> 8) & 0xFFu) - 64;
-                const int32_t zz = (int32_t)((w >> 16) & 0xFFu) - 64;
-                sx += xx;
-                sy += yy;
-                sz += zz;
-                s2 += xx * xx + yy * yy + zz * zz;
-            }
-            const int64_t gg = grown;
-            res_nn = gg * (int64_t)s2 - ((int64_t)sx * sx + (int64_t)sy * sy + (int64_t)sz * sz);
             res_ex = (int32_t)(tip & 0xFFu) - 64;
             res_ey = (int32_t)((tip >> 8) & 0xFFu) - 64;
             res_ez = (int32_t)((tip >> 16) & 0xFFu) - 64;
+            // N terms were added, the last N - grown of them the tip again
+            const int32_t dup = N - grown;
+            const int32_t bx = (int32_t)(sxz & 0xFFFFu), by = (int32_t)(sy >> 8), bz = (int32_t)(sxz >> 16);
+            const int32_t sx = bx - 64 * N - dup * res_ex, syy = by - 64 * N - dup * res_ey,
+                          sz = bz - 64 * N - dup * res_ez;
+            const int32_t ss = (int32_t)s2 - 128 * (bx + by + bz) + 3 * 4096 * N -
+                               dup * (res_ex * res_ex + res_ey * res_ey + res_ez * res_ez);
+            const int64_t gg = grown;
+            res_nn = gg * (int64_t)ss - ((int64_t)sx * sx + (int64_t)syy * syy + (int64_t)sz * sz);
             res_lw = alive ? lw : -__builtin_huge_val();
             res_wx = alive ? wx : 0ull;
             res_grown = grown;
@@ -1064,16 +1053,17 @@ __device__ __forceinline__ void grow_lattice26_lane_body(const GrowArgs &a, uint
     publish_log_w_max_block(a, bits);
 }
 
+// At least 4 waves per SIMD: the register budget of 128 VGPRs.
 template <bool EXACT, typename CT>
-__global__ __launch_bounds__(kZ26LaneThreads) void grow_lattice26_lane(GrowArgs a, uint64_t base)
+__global__ __launch_bounds__(kZ26LaneThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+grow_lattice26_lane(GrowArgs a, uint64_t base)
 {
     grow_lattice26_lane_body<EXACT, CT>(a, base + blockIdx.x);
 }
 
 template <bool EXACT, typename CT>
-__global__ __launch_bounds__(kZ26LaneThreads) void grow_lattice26_lane_batch(const GrowEntry *tab,
-                                                                            const uint64_t *block0, int n,
-                                                                            uint64_t base)
+__global__ __launch_bounds__(kZ26LaneThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+grow_lattice26_lane_batch(const GrowEntry *tab, const uint64_t *block0, int n, uint64_t base)
 {
     const uint64_t bid = base + blockIdx.x;
     const int e = find_segment(block0, n, bid);
@@ -1162,7 +1152,7 @@ hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVarian
         v->p2 = i16 ? 1 : 0;
         v->threads = kZ26LaneThreads;
         v->cpb = kZ26LaneThreads;
-        v->shmem = z26_lane_shmem(N, kZ26LaneThreads);
+        v->shmem = z26_lane_shmem(kZ26LaneThreads);
         v->H = 0;
         v->S = 0;
         return hipSuccess;
