@@ -133,30 +133,51 @@ def lattice26_alg_ops_per_chain(N: int) -> int:
     return sum(6 * max(i - 1, 0) + 8 + 20 for i in range(1, N))
 
 
+def site_set_ops_per_chain(N: int, z: int) -> int:
+    """Algorithmic VALU lane-operations of one chain grown with a site set:
+    per step one test per candidate site, 8 for the step's share of a Philox
+    block and 10 to count, pick and apply the move and tally m_i."""
+    return (N - 1) * (z + 8 + 10)
+
+
+def site_set_lds_bytes_per_chain(N: int, lookups: int) -> int:
+    """Algorithmic LDS bytes of the same: per step `lookups` buckets of 32
+    bytes are read and an entry of 8 bytes written."""
+    return (N - 1) * (32 * lookups + 8)
+
+
 def path_model(w) -> dict:
-    """Growth kernel of a workload, its algorithmic VALU lane-operations and
-    LDS bytes per launch, and the VALU peak it is priced against."""
+    """Growth kernel of a workload (as the built-in rules choose it), its
+    algorithmic VALU lane-operations and LDS bytes per launch, and the VALU
+    peak it is priced against."""
     geo, N, M = w["geometry"], w["N"], w["n_chains"]
+    vgprs = "chain history in VGPRs: no LDS traffic"
+    buckets = "one bucket read per lookup, one entry written per step"
     if geo == "lattice":
+        if N > 2048 or (N > 1024 and M >= 4096):
+            return dict(kernel="grow_lattice_set", kernel_file="grow_lattice_set.hip",
+                        ops=site_set_ops_per_chain(N, 6) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
+                        lds_bytes=site_set_lds_bytes_per_chain(N, 6) * M, lds_note=buckets)
         reg = N <= 64 or w.get("exact_w", False)
-        grp = not reg and N <= 4096  # history in the group's VGPRs (built-in lane rule)
-        kernel = "grow_lattice_reg" if reg else ("grow_lattice_grp" if grp else "grow_lattice_lds")
-        return dict(kernel=kernel, kernel_file="grow_lattice.hip" if reg else "grow_lattice_lds.hip",
+        return dict(kernel="grow_lattice_reg" if reg else "grow_lattice_grp",
+                    kernel_file="grow_lattice.hip" if reg else "grow_lattice_lds.hip",
                     ops=lattice_alg_ops_per_chain(N) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                    lds_bytes=0.0 if reg or grp else lattice_lds_bytes_per_chain(N) * M,
-                    lds_note=("chain history in VGPRs: no LDS traffic" if reg or grp else
-                              "parity-plane words of the neighbour candidates read once per step"))
+                    lds_bytes=0.0, lds_note=vgprs)
     if geo == "lattice26":
-        lane = N <= 64
-        grp = not lane and N <= 4096  # one-word formats in the group's VGPRs (built-in lane rule)
-        return dict(kernel="grow_lattice26_lane" if lane else ("grow_lattice26_grp" if grp else "grow_lattice26"),
+        if N > 300:
+            return dict(kernel="grow_lattice_set", kernel_file="grow_lattice_set.hip",
+                        ops=site_set_ops_per_chain(N, 26) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
+                        lds_bytes=site_set_lds_bytes_per_chain(N, 8) * M, lds_note=buckets)
+        return dict(kernel="grow_lattice26_lane" if N <= 64 else "grow_lattice26_grp",
                     kernel_file="grow_lattice26.hip",
                     ops=lattice26_alg_ops_per_chain(N) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                    lds_bytes=0.0 if grp else lattice26_lds_bytes_per_chain(N) * M * (1 if lane else 2),
-                    lds_note="chain history in VGPRs: no LDS traffic" if grp else "monomer words read once per step")
+                    lds_bytes=0.0, lds_note=vgprs)
+    k = w["k"]
+    queued = N >= (80 if k <= 4 else 144 if k <= 8 else 400 if k <= 16 else 500 if k <= 32 else 1000)
     hbm = N > 1536
-    return dict(kernel="grow_real_hbm" if hbm else "grow_real_tp", kernel_file="grow_real.hip",
-                ops=real_alg_ops_per_chain(N, w["k"]) * M, peak=VALU_PEAK_FP64_TOPS, int_path=False,
+    return dict(kernel="grow_real_hbm" if hbm else "grow_real_queue" if queued else "grow_real_tp",
+                kernel_file="grow_real.hip",
+                ops=real_alg_ops_per_chain(N, k) * M, peak=VALU_PEAK_FP64_TOPS, int_path=False,
                 lds_bytes=0.0 if hbm else real_lds_bytes_per_chain(N) * M,
                 lds_note="beads in HBM planes" if hbm else "beads read once per step")
 

@@ -526,10 +526,11 @@ rsaw_status rsaw_mapping_set(const rsaw_mapping *m);
  * beyond N = 128 in byte words, 26-neighbour group kernel in byte words up
  * to N = 640 and packed 11/11/10-bit words up to N = 4096): a chain whose
  * tip reaches |x|, |y| or |z| = edge is dropped from that kernel and grown
- * again, from its first draw, in two-word format by the same block.  Each
- * format has its own largest exact edge (127, 62 and 254); edge = 0 (the
- * default) uses those, 1..127 lowers every edge to at most that value,
- * which only sends more chains through the regrowth.  Results never depend
+ * again, from its first draw, in two-word format by the same block (by the
+ * group itself, without its site set, in the kernel of long chains).  Each
+ * format has its own edge (at most 127, 62 and 254; the site set's is its
+ * period); edge = 0 (the default) uses those, 1..127 lowers every edge to at
+ * most that value, which only sends more chains through the regrowth.  Results never depend
  * on it: every chain is bit-identical either way.  Process-wide; applies
  * to calls enqueued after it.  Host-only.
  * Errors: RSAW_E_INVALID unless 0 <= edge <= 127.
@@ -556,9 +557,10 @@ rsaw_status rsaw_mapping_list(rsaw_mapping *out, int32_t capacity, int32_t *coun
  * rsaw_mapping_query — the mapping a rsaw_gen_chains call with `cfg` would
  * launch its group kernel with, written to the host struct *m (n_lo =
  * n_hi = cfg->n_monomers).  Host-only, no device call.  Where the built-in
- * rule serves long simple cubic chains with the site-set kernel, which has no
- * mapping, this is the built-in mapping of the scanning kernel that a table
- * entry would select there.  Kernels without a
+ * rule serves long chains with a kernel that has no mapping (the site set of
+ * the lattices, the queued hard-sphere kernel up to N = 1536), this is the
+ * built-in mapping of the kernel that a table entry would select there.
+ * Kernels without a
  * group mapping report lanes = 1 (one lane per chain: lattice N <= 64, exact
  * weights) or lanes = 64 with lds_bytes = 0 (hard spheres beyond N = 1536,
  * bead planes in HBM).

@@ -1151,7 +1151,21 @@ static hipError_t z26_shape(int N, bool i16, int G, int threads, GrowVariant *v)
 // 1.54 ms against 4 lanes).  256-thread blocks when the block's LDS fits in
 // half a CU's, else one wave.  A legal mapping of the tuning table replaces
 // the rule for the group kernel.
-hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v)
+hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v);
+hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
+                              int n, uint64_t blocks, size_t shmem, hipStream_t s);
+
+// Calls that the site set (grow_lattice_set.hip) serves instead of the
+// scanning group kernels of this file, unless the tuning table maps the call
+// to one of them.  MI355X, kernel time, set against scan: N = 257, 5 10^5
+// chains, 5.40 / 4.94 ms; N = 300, 3 10^5, 4.17 / 4.15; N = 400, 2 10^5, 4.08 /
+// 5.44; N = 512, 2 10^5, 5.27 / 10.0; N = 1000, 10^5, 8.20 / 11.2; N = 2048,
+// 3 10^4, 11.0 / 14.5; N = 8000, 1000 chains, 4.83 / 40.0.  Small ensembles,
+// 2000 chains: N = 300, 0.25 / 0.54; N = 1000, 0.72 / 0.92; N = 4000, 2.51 / 4.73.
+// Restarts: N = 300, 5 10^4, 1.09 / 1.06.
+constexpr int kSet26MinN = 301;
+
+hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v, bool scan)
 {
     const int N = a.n_monomers;
     if (N <= kZ26LaneMax) {
@@ -1171,6 +1185,7 @@ hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVarian
     if (tuned_mapping(2 /* 26-neighbour lattice */, N, a.k_trials, &tl, &tt) &&
         z26_shape(N, i16, tl, tt, v) == hipSuccess)
         return hipSuccess;
+    if (!scan && N >= kSet26MinN) return lattice_set_variant(N, true, i16, v);
     const int G = N <= 128 ? 2 : (N <= 256 ? 4 : (N <= 512 ? 8 : (N <= 1024 ? 16 : (N <= 2048 ? 32 : 64))));
     GrowVariant half_cu;
     if (z26_shape(N, i16, G, 256, &half_cu) == hipSuccess && half_cu.shmem <= 81920) {
@@ -1285,9 +1300,10 @@ static hipError_t dispatch26(const GrowArgs &a, const GrowVariant &v, const Grow
 hipError_t launch_grow_lattice26(const GrowArgs &a, bool exact, bool i16, hipStream_t s)
 {
     GrowVariant v;
-    hipError_t e = lattice26_variant(a, exact, i16, &v);
+    hipError_t e = lattice26_variant(a, exact, i16, &v, false);
     if (e != hipSuccess) return e;
-    const uint64_t blocks = (a.n_chains + v.cpb - 1) / v.cpb;
+    const uint64_t blocks = variant_blocks(v, a.n_chains);
+    if (v.family == 4) return launch_lattice_set(a, v, nullptr, nullptr, 0, blocks, v.shmem, s);
     return dispatch26(a, v, nullptr, nullptr, 0, blocks, v.shmem, s);
 }
 

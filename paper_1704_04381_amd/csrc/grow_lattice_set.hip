@@ -47,6 +47,17 @@
 // fit in a CU's LDS.  MI355X, whole calls, scan of the history with 64 lanes or
 // in LDS -> set: N = 2048, 10^5 chains, 16.9 -> 10.9 ms; N = 10000, 5000
 // chains, 81.9 -> 7.4 ms, where the longest chain's 10^4 steps alone take 3 ms.
+//
+// 26-neighbour lattice (Z26).  The 27 sites around the tip lie in its own block
+// and at most seven others: lane t = tx + 2 ty + 4 tz takes the block that is
+// its own or the one next to it on the tip's side along each axis (none where
+// the tip is not at that face), spreads the bitmap's rows over the code
+// (dx + 1) + 3 (dy + 1) + 9 (dz + 1), and an OR over the group gives the mask.
+// Counters at N = 2048: 186 vector instructions per step of a wave (three chains
+// to a wave there, as many as the LDS holds), 0.56 of the issue slots; the scan
+// takes 329 per step of two chains.  MI355X, growth kernel, scan -> set: N = 512,
+// 2 10^5 chains, 10.0 -> 5.3 ms; N = 2048, 3 10^4, 14.5 -> 11.0; N = 8000, 1000
+// chains, 40 -> 4.8.
 #include "lattice_common.hpp"
 
 #include <type_traits>
@@ -56,6 +67,7 @@ namespace rsaw {
 constexpr uint32_t kSetMx = 0x3u | (0x1FFu << 5);
 constexpr uint32_t kSetMy = 0xCu | (0x1FFu << 14);
 constexpr uint32_t kSetMz = 0x10u | (0x1FFu << 23);
+constexpr uint32_t kSetCodes26 = 0x7FFFFFFu & ~(1u << 13); // 27 sites without the tip's own
 
 __device__ __forceinline__ void set_wave_sync()
 {
@@ -145,32 +157,70 @@ __device__ __forceinline__ int64_t sum8(int64_t v)
     return v;
 }
 
-// Move of canonical candidate j = 0..5 (-z, -y, -x, +x, +y, +z).
+// Move of candidate j: 0..5 (-z, -y, -x, +x, +y, +z), or the code of Z26.
+template <bool Z26>
 __device__ __forceinline__ void set_move(int j, int &x, int &y, int &z)
 {
-    x += (j == 3) - (j == 2);
-    y += (j == 4) - (j == 1);
-    z += (j == 5) - (j == 0);
+    if constexpr (Z26) {
+        x += j % 3 - 1;
+        y += j / 3 % 3 - 1;
+        z += j / 9 - 1;
+    } else {
+        x += (j == 3) - (j == 2);
+        y += (j == 4) - (j == 1);
+        z += (j == 5) - (j == 0);
+    }
 }
 
-// Grows chain c of this group without a set: moves as nibbles (j + 1) in
-// `mv`, eight per word; in each step lane t retraces the moves of its eighth
+// log W from the group's counts: lane t holds n_m of m = t + 2 (six
+// neighbours), or of m = t + 1 + 8 f in n[f] (Z26); `lane` reads one of them.
+template <bool Z26, typename F>
+__device__ __forceinline__ double set_sum_log_w(const GrowArgs &a, F &&lane)
+{
+    if constexpr (!Z26) {
+        return set_log_w(a, lane(0, 0), lane(1, 0), lane(2, 0), lane(3, 0));
+    } else {
+        double lw = 0.0;
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+            for (int q = 0; q < (f < 3 ? 8 : 2); ++q) lw = lw + (double)lane(q, f) * a.logm[1 + q + 8 * f];
+        return lw;
+    }
+}
+
+// Counts a step with m free candidates.
+template <bool Z26>
+__device__ __forceinline__ void set_count(uint32_t (&n)[4], uint32_t m, int t)
+{
+    if constexpr (Z26) {
+#pragma unroll
+        for (uint32_t f = 0; f < 4; ++f) n[f] += m == (uint32_t)t + 1u + 8u * f ? 1u : 0u;
+    } else {
+        n[0] += m == (uint32_t)t + 2u ? 1u : 0u;
+    }
+}
+
+// Grows chain c of this group without a set: moves (j + 1) in `mv`, a nibble
+// each (a byte in Z26); in each step lane t retraces the moves of its eighth
 // of the chain.  The group's eight lanes are active; mv is left cleared.
+template <bool Z26>
 __device__ __forceinline__ bool replay_chain(const GrowArgs &a, uint32_t *mv, uint64_t c, SetResult *out)
 {
     const int N = a.n_monomers;
     const int t = threadIdx.x & 7;
     const uint64_t g = a.chain_offset + c;
-    const int words = (N + 6) / 8;            // N - 1 moves
+    constexpr int BITS = Z26 ? 8 : 4, PER = 32 / BITS;
+    const int gbase = threadIdx.x & 56;
+    const int words = (N - 2) / PER + 1;      // N - 1 moves
     const int segw = (words + 7) / 8;         // words per lane
-    const int first = t * segw * 8;           // moves before this lane's
+    const int first = t * segw * PER;         // moves before this lane's
     bool failed = false;
     for (uint32_t rd = 0;; ++rd) {
         for (int w = t; w < words; w += 8) mv[w] = 0u;
         set_wave_sync();
         int x = 0, y = 0, z = 0;     // tip
         int px = 0, py = 0, pz = 0;  // site before this lane's first move
-        uint32_t n2 = 0, n3 = 0, n4 = 0, n5 = 0;
+        uint32_t n[4] = {0, 0, 0, 0};
         int placed = 1;
         Philox4 blk{0, 0, 0, 0};
         const uint32_t hi = rd << 16;
@@ -180,8 +230,8 @@ __device__ __forceinline__ bool replay_chain(const GrowArgs &a, uint32_t *mv, ui
             int vx = px, vy = py, vz = pz;
             for (int w = t * segw; w < (t + 1) * segw && w < words; ++w) {
                 uint32_t v = mv[w];
-                for (; v; v >>= 4) {
-                    set_move((int)(v & 15u) - 1, vx, vy, vz);
+                for (; v; v >>= BITS) {
+                    set_move<Z26>((int)(v & ((1u << BITS) - 1u)) - 1, vx, vy, vz);
                     f(vx, vy, vz);
                 }
             }
@@ -191,12 +241,17 @@ __device__ __forceinline__ bool replay_chain(const GrowArgs &a, uint32_t *mv, ui
             uint32_t occ = 0;
             visit([&](int vx, int vy, int vz) {
                 const int dx = vx - x, dy = vy - y, dz = vz - z;
-                const int l1 = (dx < 0 ? -dx : dx) + (dy < 0 ? -dy : dy) + (dz < 0 ? -dz : dz);
-                const int q = dx + 2 * dy + 3 * dz; // -3..3
-                if (l1 == 1) occ |= 1u << (q < 0 ? q + 3 : q + 2);
+                if constexpr (Z26) {
+                    if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1)
+                        occ |= 1u << (dx + 1 + 3 * (dy + 1) + 9 * (dz + 1));
+                } else {
+                    const int l1 = (dx < 0 ? -dx : dx) + (dy < 0 ? -dy : dy) + (dz < 0 ? -dz : dz);
+                    const int q = dx + 2 * dy + 3 * dz; // -3..3
+                    if (l1 == 1) occ |= 1u << (q < 0 ? q + 3 : q + 2);
+                }
             });
             occ = or8(occ);
-            const uint32_t freem = ~occ & 0x3Fu, m = __builtin_popcount(freem);
+            const uint32_t freem = ~occ & (Z26 ? kSetCodes26 : 0x3Fu), m = __builtin_popcount(freem);
             if (i == 1 || (i & 7) == 0) blk = draw(a.seed, g, (uint32_t)(i >> 3) | hi, kSlotSelect, 0);
             const uint32_t xw = half_word(blk, (uint32_t)(i & 7));
             if (m == 0) {
@@ -211,18 +266,15 @@ __device__ __forceinline__ bool replay_chain(const GrowArgs &a, uint32_t *mv, ui
             uint32_t f = freem;
             for (; r; --r) f &= f - 1u;
             const int j = __builtin_ctz(f);
-            set_move(j, x, y, z);
-            if (t == 0) mv[(i - 1) >> 3] |= (uint32_t)(j + 1) << (4 * ((i - 1) & 7));
+            set_move<Z26>(j, x, y, z);
+            if (t == 0) mv[(i - 1) / PER] |= (uint32_t)(j + 1) << (BITS * ((i - 1) & (PER - 1)));
             set_wave_sync();
             if (i == first) {
                 px = x;
                 py = y;
                 pz = z;
             }
-            n2 += m == 2;
-            n3 += m == 3;
-            n4 += m == 4;
-            n5 += m == 5;
+            set_count<Z26>(n, m, t);
             ++placed;
         }
         if (dead && rd + 1 < a.max_rounds) continue;
@@ -238,7 +290,9 @@ __device__ __forceinline__ bool replay_chain(const GrowArgs &a, uint32_t *mv, ui
         sz = sum8(sz);
         s2 = sum8(s2);
         out->nn = (int64_t)placed * s2 - (sx * sx + sy * sy + sz * sz);
-        out->lw = dead ? -__builtin_huge_val() : set_log_w(a, n2, n3, n4, n5);
+        const double lw =
+            set_sum_log_w<Z26>(a, [&](int q, int f) { return (uint32_t)__shfl(n[f], gbase + q, 64); });
+        out->lw = dead ? -__builtin_huge_val() : lw;
         out->x = x;
         out->y = y;
         out->z = z;
@@ -261,7 +315,7 @@ __host__ __device__ inline uint32_t set_chunk(uint64_t n_chains, uint32_t gpw, u
     return c < 1 ? 1u : (c > 64 ? 64u : (uint32_t)c);
 }
 
-template <typename CT>
+template <bool Z26, typename CT>
 __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_t NB, uint32_t gpw)
 {
     extern __shared__ uint4 set_lds[];
@@ -278,12 +332,22 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
     const uint32_t chunk = set_chunk(a.n_chains, gpw, NB);
 
     // this lane's candidate: the axis' field mask and the addend of its move
-    const bool cand = t < 6;
+    const bool cand = Z26 || t < 6;
     const int axis = t == 0 || t == 5 ? 2 : (t == 1 || t == 4 ? 1 : 0);
     const uint32_t fm = axis == 0 ? kSetMx : (axis == 1 ? kSetMy : kSetMz);
     const uint32_t fn = ~fm;
     const uint32_t fd = !cand ? 0u : (t < 3 ? fm : (fm & (0u - fm)));
     const uint32_t below = (1u << t) - 1u;
+    // Z26: key addends of this lane's block, and per place of the tip in its
+    // block (a byte each) the shifts that take the bitmap's rows to the code
+    const bool ox = t & 1, oy = (t >> 1) & 1, oz = t >> 2;
+    const uint32_t px1 = ox ? 1u << 5 : 0u, mx1 = ox ? 0x1FFu << 5 : 0u;
+    const uint32_t py1 = oy ? 1u << 14 : 0u, my1 = oy ? 0x1FFu << 14 : 0u;
+    const uint32_t pz1 = oz ? 1u << 23 : 0u, mz1 = oz ? 0x1FFu << 23 : 0u;
+    const uint32_t nowhere = (ox ? 1u : 0u) | (oy ? 4u : 0u); // of P ^ (P >> 1): not at a face
+    const uint32_t shx = ox ? 0x01000006u : 0x05040302u;      // right, rows pre-shifted by 3
+    const uint32_t shyl = oy ? 0x10000000u : 0x00000008u, shyr = oy ? 0x00000018u : 0x10080000u;
+    const uint32_t shzl = oz ? 0x00001200u : 0x00000009u, shzr = oz ? 0x00000009u : 0u;
     uint32_t nb = NB; // in a VGPR: the step loop has scalar registers to spare for masks only
     asm volatile("" : "+v"(nb));
     // its coordinate's fields: low bits, high bits, width
@@ -305,7 +369,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
     bool full = false;          // this lane found no room for a block
     bool rng_fail = false;
     uint64_t c = 0, best = 0;
-    uint32_t rd = 0, i0 = 0, P = 0, n_mine = 0;
+    uint32_t rd = 0, i0 = 0, P = 0, n_mine[4] = {0, 0, 0, 0};
     int placed = 1, co = 0, cmin = 0, cmax = 0;
     uint32_t fprev = 0;
 
@@ -314,7 +378,8 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
         i0 = 0;
         P = 0;
         placed = 1;
-        n_mine = 0;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) n_mine[f] = 0;
         co = cmin = cmax = 0;
         fprev = 0;
         // the origin's entry
@@ -392,9 +457,9 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
                 r.z = co;
                 r.grown = placed;
                 if (r.alive)
-                    r.lw = set_log_w(a, n_mine, __builtin_amdgcn_readlane(n_mine, src + 1),
-                                     __builtin_amdgcn_readlane(n_mine, src + 2),
-                                     __builtin_amdgcn_readlane(n_mine, src + 3));
+                    r.lw = set_sum_log_w<Z26>(a, [&](int q, int f) {
+                        return (uint32_t)__builtin_amdgcn_readlane((int)n_mine[f], src + q);
+                    });
                 set_write<CT>(a, c, r);
                 const uint64_t bits = r.alive ? (uint64_t)__double_as_longlong(r.lw) : 0ull;
                 best = bits > best ? bits : best;
@@ -404,7 +469,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(fail) != 0, 0)) {
             if (fail) {
                 SetResult r;
-                rng_fail = replay_chain(a, (uint32_t *)tab, c, &r) || rng_fail;
+                rng_fail = replay_chain<Z26>(a, (uint32_t *)tab, c, &r) || rng_fail;
                 if (t == 0) {
                     set_write<CT>(a, c, r);
                     const uint64_t bits = r.alive ? (uint64_t)__double_as_longlong(r.lw) : 0ull;
@@ -462,8 +527,19 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
         static_for<0, 8>([&](auto E) {
             constexpr int e = E.value;
             const uint32_t act = 0u - ((ticks >> e) & 1u);
-            const uint32_t C = (((P | fn) + fd) & fm) | (P & fn);
-            const uint32_t kk = C | 31u;
+            uint32_t C = 0, kk, looks = act; // the candidate site, the key, whether the lookup counts
+            if constexpr (Z26) {
+                const auto side = [&](uint32_t bit, uint32_t up, uint32_t down) {
+                    const uint32_t high = (uint32_t)((int)(P << (31 - bit)) >> 31);
+                    return P + __builtin_amdgcn_bitop3_b32(high, up, down, 0xCA); // high ? up : down
+                };
+                kk = (side(1, px1, mx1) & (kSetMx & ~31u)) | (side(3, py1, my1) & (kSetMy & ~31u)) |
+                     (side(4, pz1, mz1) & (kSetMz & ~31u)) | 31u;
+                looks = ((P ^ (P >> 1)) & nowhere) ? 0u : act;
+            } else {
+                C = (((P | fn) + fd) & fm) | (P & fn);
+                kk = C | 31u;
+            }
             // a bucket's entries: (x, y), (z, w) of q0 and q1
             const uint4 *b = tab + 2 * set_home(kk, nb);
             uint4 q0, q1;
@@ -479,7 +555,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
                 return q1.z == kk ? q1.w : f;
             };
             uint32_t bm = look();
-            const uint32_t more = (bm == 0u ? q1.z : 0u) & act; // not found, no room
+            const uint32_t more = (bm == 0u ? q1.z : 0u) & looks; // not found, no room
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(more != 0u) != 0, 0)) {
                 if (more != 0u) {
                     int left = kSetProbes;
@@ -494,9 +570,26 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
                     } while (bm == 0u && q1.z != 0u);
                 }
             }
-            const uint32_t fr = ~(bm >> (C & 31u)) & act & 1u;
-            const uint64_t bal = __builtin_amdgcn_ballot_w64(fr != 0u);
-            const uint32_t mask = (uint32_t)(bal >> gbase) & 0x3Fu;
+            // free candidates: a bit per lane, or per code
+            uint32_t fr = 0, mask;
+            if constexpr (Z26) {
+                const uint32_t ix = (P & 3u) << 3, iy = (P & 12u) << 1, iz = (P & 16u) >> 1;
+                const uint32_t sx = shx >> ix, yl = shyl >> iy, yr = shyr >> iy;
+                const auto plane = [&](uint32_t p) { // 16 bits, rows of 4 along x -> 9 bits of (dx, dy)
+                    p = (p | (p << 8)) & 0x00FF00FFu;
+                    p = (p | (p << 4)) & 0x0F0F0F0Fu;
+                    p = ((p << 3) >> (sx & 31u)) & 0x07070707u;
+                    p = (p << (yl & 31u)) >> (yr & 31u);
+                    return __builtin_amdgcn_udot4(p, 0x00400801u, 0u, false);
+                };
+                uint32_t occ = plane(bm & 0xFFFFu) | (plane(bm >> 16) << 9);
+                occ = (occ << ((shzl >> iz) & 31u)) >> ((shzr >> iz) & 31u);
+                mask = ~or8(occ & looks) & kSetCodes26 & act;
+            } else {
+                fr = ~(bm >> (C & 31u)) & act & 1u;
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(fr != 0u);
+                mask = (uint32_t)(bal >> gbase) & 0x3Fu;
+            }
             const uint32_t m = __builtin_popcount(mask);
             const uint32_t x = half_word(blk, (uint32_t)e);
             const uint32_t p = x * m;
@@ -511,7 +604,28 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
                     }
                 }
             }
-            const bool chosen = (fr != 0u) & ((uint32_t)__builtin_popcount(mask & below) == r);
+            const bool ok = m != 0u;
+            bool chosen;
+            uint32_t NP = 0;
+            if constexpr (Z26) {
+                // the r-th free code: lane t looks among codes 4 t .. 4 t + 3
+                const uint32_t four = (mask >> (4 * t)) & 15u;
+                const uint32_t k = r - (uint32_t)__builtin_popcount(mask & ((1u << (4 * t)) - 1u));
+                const uint32_t f1 = four & (four - 1u), f2 = f1 & (f1 - 1u), f3 = f2 & (f2 - 1u);
+                const uint32_t pick = k == 0u ? four : (k == 1u ? f1 : (k == 2u ? f2 : f3));
+                const bool here = k < (uint32_t)__builtin_popcount(four);
+                const uint32_t code = or8(here ? 4u * t + (uint32_t)__builtin_ctz(pick | 16u) + 1u : 0u) - 1u;
+                const uint32_t z = (code * 57u) >> 9, rem = code - 9u * z, y = (rem * 11u) >> 5, xx = rem - 3u * y;
+                const auto moved = [&](uint32_t d, uint32_t field) {
+                    const uint32_t add = d == 0u ? field : (d == 2u ? field & (0u - field) : 0u);
+                    return ((P | ~field) + add) & field;
+                };
+                NP = moved(xx, kSetMx) | moved(y, kSetMy) | moved(z, kSetMz);
+                C = NP;
+                chosen = ok & (kk == (NP | 31u)); // the lane that looked its block up
+            } else {
+                chosen = (fr != 0u) & ((uint32_t)__builtin_popcount(mask & below) == r);
+            }
             // written to its entry or the first empty one; the other lanes
             // write to their places behind the tables, which costs less than
             // a branch around the store
@@ -522,11 +636,10 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
             uint2 *at = (uint2 *)b + o;
             at = chosen ? at : spare;
             *at = make_uint2(kk, bm | (1u << (C & 31u)));
-            const uint32_t NP = or8(chosen ? C : 0u);
-            const bool ok = m != 0u;
+            if constexpr (!Z26) NP = or8(chosen ? C : 0u);
             P = ok ? NP : P;
             placed += ok ? 1 : 0;
-            n_mine += m == (uint32_t)t + 2u ? 1u : 0u;
+            set_count<Z26>(n_mine, m, t);
             // a dead end closes the run (the tick of step 0 is none)
             ticks = (e == 0 ? ok || i0 == 0 : ok) ? ticks : 0u;
             set_wave_sync();
@@ -538,37 +651,38 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
     publish_log_w_max(a, best);
 }
 
-template <typename CT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+template <bool Z26, typename CT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Z26 ? 3 : 4, 8))) void
 grow_lattice_set(GrowArgs a, uint32_t NB, uint32_t gpw)
 {
-    grow_lattice_set_body<CT>(a, NB, gpw);
+    grow_lattice_set_body<Z26, CT>(a, NB, gpw);
 }
 
 // Batched launch: block b serves the ensemble whose block range holds b.
-template <typename CT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+template <bool Z26, typename CT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Z26 ? 3 : 4, 8))) void
 grow_lattice_set_batch(const GrowEntry *tab, const uint64_t *block0, int n, uint64_t base)
 {
     const int e = find_segment(block0, n, base + blockIdx.x);
-    grow_lattice_set_body<CT>(tab[e].a, (uint32_t)tab[e].H, (uint32_t)tab[e].S);
+    grow_lattice_set_body<Z26, CT>(tab[e].a, (uint32_t)tab[e].H, (uint32_t)tab[e].S);
 }
 
-// Table of a chain of N monomers: it has N / 4.6 (N = 256) to N / 5.3
+// Table of a chain of N monomers.  Six neighbours: N / 4.6 (N = 256) to N / 5.3
 // (N = 10000) blocks, standard deviation below 0.57 sqrt(N) (measured), and
-// gets 0.35 N entries, a load of 0.62 to 0.54.  Chains per wave: what a CU's
+// 0.35 N entries, a load of 0.62 to 0.54; 26 neighbours: N / 3.3 (N = 256) to
+// N / 3.6 (N = 2048) blocks, and 0.53 N entries.  Chains per wave: what a CU's
 // LDS holds over eight waves (two per SIMD), at most eight; fewer chains per
 // wave where the LDS holds few, since a wave waits for the slowest lookup of
 // its chains.
-hipError_t lattice_set_variant(int N, bool i16, GrowVariant *v)
+hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v)
 {
-    const int NB = N * 7 / 80 + 6;
+    const int NB = (z26 ? N * 53 / 400 : N * 7 / 80) + 6;
     const int fit = (163840 - 8 * (int)kSetSpare) / (NB * 32); // chains per CU
     int gpw = (fit + 7) / 8;
     gpw = gpw < 1 ? 1 : (gpw > 8 ? 8 : gpw);
     v->family = 4;
     v->p0 = 8;
-    v->p1 = 0;
+    v->p1 = z26 ? 1 : 0;
     v->p2 = i16 ? 1 : 0;
     v->threads = 64;
     v->cpb = gpw;
@@ -579,26 +693,32 @@ hipError_t lattice_set_variant(int N, bool i16, GrowVariant *v)
     return hipSuccess;
 }
 
-hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
-                              int n, uint64_t blocks, size_t shmem, hipStream_t s)
+template <bool Z26, typename CT>
+static hipError_t launch_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
+                             int n, uint64_t blocks, size_t shmem, hipStream_t s)
 {
-    const void *fn = tab ? (v.p2 ? (const void *)grow_lattice_set_batch<int16_t>
-                                 : (const void *)grow_lattice_set_batch<int32_t>)
-                         : (v.p2 ? (const void *)grow_lattice_set<int16_t> : (const void *)grow_lattice_set<int32_t>);
+    const void *fn = tab ? (const void *)grow_lattice_set_batch<Z26, CT> : (const void *)grow_lattice_set<Z26, CT>;
     if (shmem > 65536) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
         if (e != hipSuccess) return e;
     }
     return launch_sliced(blocks, 64, [&](uint64_t b0, uint32_t nb) {
-        const dim3 gr(nb), bl(64);
-        if (tab) {
-            if (v.p2) hipLaunchKernelGGL((grow_lattice_set_batch<int16_t>), gr, bl, shmem, s, tab, block0, n, b0);
-            else hipLaunchKernelGGL((grow_lattice_set_batch<int32_t>), gr, bl, shmem, s, tab, block0, n, b0);
-        } else {
-            if (v.p2) hipLaunchKernelGGL((grow_lattice_set<int16_t>), gr, bl, shmem, s, a, (uint32_t)v.H, (uint32_t)v.S);
-            else hipLaunchKernelGGL((grow_lattice_set<int32_t>), gr, bl, shmem, s, a, (uint32_t)v.H, (uint32_t)v.S);
-        }
+        if (tab)
+            hipLaunchKernelGGL((grow_lattice_set_batch<Z26, CT>), dim3(nb), dim3(64), shmem, s, tab, block0, n, b0);
+        else
+            hipLaunchKernelGGL((grow_lattice_set<Z26, CT>), dim3(nb), dim3(64), shmem, s, a, (uint32_t)v.H,
+                               (uint32_t)v.S);
     });
+}
+
+hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
+                              int n, uint64_t blocks, size_t shmem, hipStream_t s)
+{
+    if (v.p1)
+        return v.p2 ? launch_set<true, int16_t>(a, v, tab, block0, n, blocks, shmem, s)
+                    : launch_set<true, int32_t>(a, v, tab, block0, n, blocks, shmem, s);
+    return v.p2 ? launch_set<false, int16_t>(a, v, tab, block0, n, blocks, shmem, s)
+                : launch_set<false, int32_t>(a, v, tab, block0, n, blocks, shmem, s);
 }
 
 } // namespace rsaw

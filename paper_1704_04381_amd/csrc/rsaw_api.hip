@@ -40,7 +40,7 @@ hipError_t launch_lattice_lds_batch(const GrowVariant &v, const GrowEntry *tab, 
 hipError_t launch_real_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
                              uint64_t blocks, size_t shmem, hipStream_t s);
 int lattice26_max_monomers();
-hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v);
+hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v, bool scan);
 hipError_t launch_grow_lattice26(const GrowArgs &a, bool exact, bool i16, hipStream_t s);
 hipError_t launch_lattice26_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
                                   uint64_t blocks, size_t shmem, hipStream_t s);
@@ -493,7 +493,7 @@ hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::Gr
     probe.max_rounds = (cfg->flags & RSAW_RESTART) ? 65536u : 1u;
     const bool i16 = cfg->coord_type == RSAW_I16;
     if (!L.lattice) return rsaw::real_variant(probe, v, scan);
-    if (L.z26) return rsaw::lattice26_variant(probe, L.exact, i16, v);
+    if (L.z26) return rsaw::lattice26_variant(probe, L.exact, i16, v, scan);
     if (L.exact || cfg->n_monomers <= 64) {
         rsaw::lattice_reg_variant(probe, L.exact, i16, v);
         return hipSuccess;

@@ -1,5 +1,5 @@
-"""The site-set kernel of long simple cubic chains against the oracle, bit for
-bit (Sec. 3.3.2): the edges of the rule that selects it, chains per wave from
+"""The site-set kernel of long lattice chains against the oracle, bit for bit
+(Sec. 3.3.2), on the simple cubic and the 26-neighbour lattice: the edges of the rule that selects it, chains per wave from
 eight to one, restarts, chain offsets past 2^32, ensembles smaller than a
 wave, several ensembles in a launch, and, with the byte box lowered, chains
 that are grown again without the set.  The calls repeat within a process, so
@@ -40,17 +40,35 @@ def test_site_set_bit_exact(N, M, seed, coord, edge, offset, restart):
     _lattice_case(N, M, seed, coord=coord, bins=64, offset=offset, restart=restart)
 
 
+@pytest.mark.parametrize("N,M,seed,coord,edge,offset,restart", [
+    (301, 500, 221, "i16", 0, 0, False),      # the rule's shortest chains
+    (301, 9, 222, "i32", 0, (1 << 32) + 3, True),
+    (700, 100, 223, "i32", 0, 0, False),
+    (2_049, 12, 224, "i16", 0, 0, False),     # three chains per wave
+    (9_000, 3, 225, "i32", 0, 0, False),      # one chain per wave
+    (310, 150, 226, "i16", 25, 0, False),     # some chains without the set
+    (400, 40, 227, "i32", 1, 5, True),        # all of them
+])
+def test_site_set26_bit_exact(N, M, seed, coord, edge, offset, restart):
+    from test_gpu_lattice26 import _case
+    rs.set_byte_box(edge)
+    _case(N, M, seed, coord=coord, bins=64, offset=offset, restart=restart)
+
+
 def test_site_set_in_a_batch():
     specs = [dict(geometry="lattice", N=2_200, k=6, n_chains=60, seed=211),
              dict(geometry="lattice", N=3_000, k=6, n_chains=20, seed=212, coord="i16"),
              dict(geometry="lattice", N=1_026, k=6, n_chains=130, seed=213, restart=True),
-             dict(geometry="lattice", N=300, k=6, n_chains=100, seed=214)]
+             dict(geometry="lattice", N=300, k=6, n_chains=100, seed=214),
+             dict(geometry="lattice26", N=330, k=26, n_chains=90, seed=215),
+             dict(geometry="lattice26", N=900, k=26, n_chains=20, seed=216, coord="i16")]
     for _ in range(2):
         print("[gpu] site-set batch", flush=True)
         res = rs.gen_batch(specs)
         torch.cuda.synchronize()
         for sp, (out, s) in zip(specs, res):
-            ref = oracle.gen_lattice(sp["seed"], sp["N"], sp["n_chains"], restart=sp.get("restart", False))
+            ref = oracle.gen_lattice(sp["seed"], sp["N"], sp["n_chains"], restart=sp.get("restart", False),
+                                     z26=sp["geometry"] == "lattice26")
             np.testing.assert_array_equal(out["n_grown"].cpu().numpy().view(np.uint16), ref["n_grown"])
             np.testing.assert_array_equal(out["log_w"].cpu().numpy(), ref["log_w"])
             np.testing.assert_array_equal(out["r_end"].cpu().numpy().astype(np.int32), ref["r_end"])
