@@ -608,8 +608,7 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         e = ensemble_variant(&cfgs[i], L[i], &var[i]);
         if (e != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "ensemble " + std::to_string(i) + ": no kernel variant");
     }
-    // ensembles with chains, grouped by variant (stable: index order within a
-    // group).  A launch gives every block the largest LDS of its ensembles.
+    // ensembles with chains, grouped by variant.  A launch gives every block the largest LDS of its ensembles.
     // An ensemble that fills the GPU by itself (at least one block per slot
     // that its own LDS leaves on every CU: 160 KiB / shmem per CU, capped at
     // the 32 waves a CU holds) shares a launch only with ensembles of the
@@ -635,7 +634,14 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         const rsaw::GrowVariant &v = var[i];
         return std::make_tuple(v.family, v.p0, v.p1, v.p2, v.threads, per_cu[i]);
     };
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return key(x) < key(y); });
+    // within a launch the longest chains first: blocks start in this order, and a
+    // block of long chains started last would run on alone while the GPU empties
+    // (256 ensembles of both geometries, index order -> this: 4.20 -> 3.80 ms;
+    // 222 of them 2.77 -> 2.41; 31, which start at once anyway, 0.68 either way)
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        const auto kx = key(x), ky = key(y);
+        return kx != ky ? kx < ky : cfgs[x].n_monomers > cfgs[y].n_monomers;
+    });
     const int32_t ng = (int32_t)order.size();
 
     // device tables after the ensembles' regions
