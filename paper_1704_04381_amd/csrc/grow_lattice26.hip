@@ -1151,7 +1151,7 @@ static hipError_t z26_shape(int N, bool i16, int G, int threads, GrowVariant *v)
 // 1.54 ms against 4 lanes).  256-thread blocks when the block's LDS fits in
 // half a CU's, else one wave.  A legal mapping of the tuning table replaces
 // the rule for the group kernel.
-hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v);
+hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, GrowVariant *v);
 hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                               int n, uint64_t blocks, size_t shmem, hipStream_t s);
 
@@ -1185,7 +1185,7 @@ hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVarian
     if (tuned_mapping(2 /* 26-neighbour lattice */, N, a.k_trials, &tl, &tt) &&
         z26_shape(N, i16, tl, tt, v) == hipSuccess)
         return hipSuccess;
-    if (!scan && N >= kSet26MinN) return lattice_set_variant(N, true, i16, v);
+    if (!scan && N >= kSet26MinN) return lattice_set_variant(N, a.n_chains, true, i16, v);
     const int G = N <= 128 ? 2 : (N <= 256 ? 4 : (N <= 512 ? 8 : (N <= 1024 ? 16 : (N <= 2048 ? 32 : 64))));
     GrowVariant half_cu;
     if (z26_shape(N, i16, G, 256, &half_cu) == hipSuccess && half_cu.shmem <= 81920) {

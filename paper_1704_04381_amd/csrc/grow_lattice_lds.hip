@@ -816,7 +816,7 @@ static hipError_t lds_shape(int N, bool i16, int G, int threads, GrowVariant *v)
     return lds_shape_fmt(N, i16, G, threads, true, v);
 }
 
-hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v);
+hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, GrowVariant *v);
 hipError_t launch_lattice_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                               int n, uint64_t blocks, size_t shmem, hipStream_t s);
 
@@ -851,7 +851,7 @@ hipError_t lattice_lds_variant(const GrowArgs &a, bool i16, GrowVariant *v, bool
     if (tuned_mapping(0 /* simple cubic lattice */, N, a.k_trials, &tl, &tt) &&
         lds_shape(N, i16, tl, tt, v) == hipSuccess)
         return hipSuccess;
-    if (!scan && use_site_set(a)) return lattice_set_variant(N, false, i16, v);
+    if (!scan && use_site_set(a)) return lattice_set_variant(N, a.n_chains, false, i16, v);
     const int G = N <= 128 ? 2 : N <= 256 ? 4 : (N <= 512 ? 8 : (N <= 1024 ? 16 : (N <= 2048 ? 32 : 64)));
     // wide words past N = 4096: eight chains of 32 lanes in one 256-thread
     // block per CU while they fit (N = 2200, before the registers took

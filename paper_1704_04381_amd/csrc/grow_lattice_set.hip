@@ -12,7 +12,7 @@
 //
 // Set.  Open addressing over NB buckets of 32 bytes, four entries each:
 // (P | 31 of the block, bitmap of its 32 sites); 0 is an empty entry.  A
-// chain has one entry per 4.6-5.3 monomers, so that the set takes 2.8 bytes
+// chain has one entry per 4.6-5.3 monomers, so that the set takes 2.4-3.2 bytes
 // per monomer where a history word takes 4 or 8 and its scan reads half of
 // them each step.  Entries are never moved, and buckets fill in order, so a
 // lookup ends at the block's entry or at the first empty one, which is also
@@ -45,21 +45,19 @@
 // Bound by the latency of a step (about 750 cycles: one dependent LDS read,
 // 40 % of it, and 62 vector instructions) at the number of chains whose tables
 // fit in a CU's LDS.  MI355X, whole calls, scan of the history with 64 lanes or
-// in LDS -> set: N = 2048, 10^5 chains, 16.9 -> 10.9 ms; N = 10000, 5000
-// chains, 81.9 -> 7.4 ms, where the longest chain's 10^4 steps alone take 3 ms.
+// in LDS -> set: N = 2048, 10^5 chains, 16.9 -> 9.6 ms; N = 10000, 5000
+// chains, 81.9 -> 6.7 ms, where the longest chain's 10^4 steps alone take 3 ms.
 //
 // 26-neighbour lattice (Z26).  The 27 sites around the tip lie in its own block
 // and at most seven others: lane t = tx + 2 ty + 4 tz takes the block that is
 // its own or the one next to it on the tip's side along each axis (none where
 // the tip is not at that face), spreads the bitmap's rows over the code
 // (dx + 1) + 3 (dy + 1) + 9 (dz + 1), and an OR over the group gives the mask.
-// Counters at N = 2048: 186 vector instructions per step of a wave (three chains
-// to a wave there, as many as the LDS holds), 0.56 of the issue slots; the scan
-// takes 329 per step of two chains.  MI355X, growth kernel, scan -> set: N = 512,
-// 2 10^5 chains, 10.0 -> 5.3 ms; N = 2048, 3 10^4, 14.5 -> 11.0; N = 8000, 1000
-// chains, 40 -> 4.8.
+// MI355X, growth kernel, scan -> set: N = 512, 2 10^5 chains, 10.0 -> 5.1 ms;
+// N = 2048, 3 10^4, 14.5 -> 7.5; N = 8000, 1000 chains, 40 -> 4.8.
 #include "lattice_common.hpp"
 
+#include <tuple>
 #include <type_traits>
 
 namespace rsaw {
@@ -667,19 +665,42 @@ grow_lattice_set_batch(const GrowEntry *tab, const uint64_t *block0, int n, uint
     grow_lattice_set_body<Z26, CT>(tab[e].a, (uint32_t)tab[e].H, (uint32_t)tab[e].S);
 }
 
-// Table of a chain of N monomers.  Six neighbours: N / 4.6 (N = 256) to N / 5.3
-// (N = 10000) blocks, standard deviation below 0.57 sqrt(N) (measured), and
-// 0.35 N entries, a load of 0.62 to 0.54; 26 neighbours: N / 3.3 (N = 256) to
-// N / 3.6 (N = 2048) blocks, and 0.53 N entries.  Chains per wave: what a CU's
-// LDS holds over eight waves (two per SIMD), at most eight; fewer chains per
-// wave where the LDS holds few, since a wave waits for the slowest lookup of
-// its chains.
-hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v)
+// Tables.  A chain of N monomers has N / 4.6 (N = 256) to N / 5.3 (N = 10000)
+// blocks, standard deviation below 0.57 sqrt(N) (measured), with 26 neighbours
+// N / 3.3 (N = 256) to N / 3.6 (N = 2048).  Its table has at least 0.30 N or
+// 0.39 N entries, a load of at most 0.72, and the chains per wave and the waves
+// are those that put most chains on a CU: a step's latency hardly depends on
+// either, so the chains in flight set the rate.  Of equal ones, a wave per SIMD
+// but no more than it takes, then the larger tables, up to 0.40 N or 0.53 N
+// entries, which few chains get in any case (their rate is the latency's).  MI355X, growth kernel, 0.35 N and 0.53 N entries with
+// two waves per SIMD -> this: N = 2048, 10^5 chains, 10.8 -> 9.5 ms; N = 5000,
+// 2 10^4, 9.0 -> 7.7; N = 10000, 5000, 7.3 -> 6.6; 26 neighbours N = 700, 10^5,
+// 4.5 -> 4.1; N = 2048, 3 10^4, 11.1 -> 7.5; N = 8000, 4000, 18.8 -> 14.8.
+// Smaller tables still (0.24 N) were slower at N = 1100 and 2048 (3.9, 10.1 ms).
+constexpr int kSetLds = 163840, kSetLdsUnit = 1280; // per CU, and the step in which it is given
+
+hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, GrowVariant *v)
 {
-    const int NB = (z26 ? N * 53 / 400 : N * 7 / 80) + 6;
-    const int fit = (163840 - 8 * (int)kSetSpare) / (NB * 32); // chains per CU
-    int gpw = (fit + 7) / 8;
-    gpw = gpw < 1 ? 1 : (gpw > 8 ? 8 : gpw);
+    const int least = N * (z26 ? 39 : 30) / 400 + 6, most = N * (z26 ? 53 : 40) / 400 + 6;
+    const int waves = z26 ? 12 : 16; // that the registers allow on a CU
+    const uint64_t share = (n_chains + 255) / 256;
+    const int need = share < 128 ? (int)share : 128; // chains a CU gets; it holds 16 x 8 at most
+    int gpw = 0, per_cu = 0, NB = 0;
+    std::tuple<int, int, int, int> best(0, 0, 0, 0);
+    for (int b = 1; b <= waves; ++b)
+        for (int g = 1; g <= 8; ++g) {
+            const int room = (kSetLds / kSetLdsUnit / b * kSetLdsUnit - (int)kSetSpare) / (32 * g);
+            const int nb = room < most ? room : most;
+            if (nb < least) break;
+            const std::tuple<int, int, int, int> score(g * b < need ? g * b : need, b < 4 ? b : 4, -b, nb);
+            if (score >= best) { // then the chains per wave, for batches of small ensembles
+                best = score;
+                gpw = g;
+                per_cu = b;
+                NB = nb;
+            }
+        }
+    if (gpw == 0) return hipErrorInvalidValue;
     v->family = 4;
     v->p0 = 8;
     v->p1 = z26 ? 1 : 0;
@@ -689,7 +710,7 @@ hipError_t lattice_set_variant(int N, bool z26, bool i16, GrowVariant *v)
     v->shmem = (size_t)gpw * NB * 32 + kSetSpare;
     v->H = NB;
     v->S = gpw;
-    v->max_blocks = 256u * (uint32_t)(163840 / v->shmem);
+    v->max_blocks = 256u * (uint32_t)per_cu;
     return hipSuccess;
 }
 
