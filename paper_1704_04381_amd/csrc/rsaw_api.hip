@@ -40,6 +40,7 @@ hipError_t launch_lattice_lds_batch(const GrowVariant &v, const GrowEntry *tab, 
 hipError_t launch_real_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
                              uint64_t blocks, size_t shmem, hipStream_t s);
 int lattice26_max_monomers();
+hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, GrowVariant *v);
 hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v, bool scan);
 hipError_t launch_grow_lattice26(const GrowArgs &a, bool exact, bool i16, hipStream_t s);
 hipError_t launch_lattice26_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
@@ -608,6 +609,16 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         e = ensemble_variant(&cfgs[i], L[i], &var[i]);
         if (e != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "ensemble " + std::to_string(i) + ": no kernel variant");
     }
+    // site sets share the GPU's LDS: their tables are sized for all of the
+    // batch's such chains together, not for one ensemble's
+    uint64_t set_chains = 0;
+    for (int32_t i = 0; i < n; ++i)
+        if (var[i].family == 4) set_chains += cfgs[i].n_chains;
+    for (int32_t i = 0; i < n; ++i)
+        if (var[i].family == 4 &&
+            rsaw::lattice_set_variant(cfgs[i].n_monomers, set_chains, var[i].p1 != 0, var[i].p2 != 0, &var[i]) !=
+                hipSuccess)
+            return fail(RSAW_E_UNSUPPORTED, "ensemble " + std::to_string(i) + ": no kernel variant");
     // ensembles with chains, grouped by variant.  A launch gives every block the largest LDS of its ensembles.
     // An ensemble that fills the GPU by itself (at least one block per slot
     // that its own LDS leaves on every CU: 160 KiB / shmem per CU, capped at
