@@ -75,7 +75,9 @@ def lattice_alg_ops_per_chain(N: int) -> int:
     each (L1 distance, neighbour flag, direction code, mask insert); one
     eighth of a Philox4x32-10 block, the 16 bits the pick consumes (10
     rounds x 6 operations / 8, rounded up to 8); and 10 operations to
-    count, pick and apply the move and tally m_i for log W.
+    count, pick and apply the move and tally m_i for log W.  The kernels' pair
+    test takes 2 operations, so their rate in this model's operations can
+    exceed the issue rate.
     """
     return sum(4 * (i // 2) + 8 + 10 for i in range(1, N))
 

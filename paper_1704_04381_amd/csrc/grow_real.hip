@@ -550,15 +550,21 @@ __global__ __launch_bounds__(256) void grow_real_tp_batch(const GrowEntry *tab, 
 // Directions.  With kp = the power of two >= k, a group has PH = G / kp (at
 // most 8) sets of trial lanes: lane t draws trial t mod kp of the steps
 // i = t / kp (mod PH), ahead through a two-entry queue, and owns that trial's
-// candidate when such a step comes.  One production round then serves PH
-// steps of every chain (0.4 rounds per step at PH = 4, where a round per step
-// spread over the attempts of one step took 1.1).
+// candidate when such a step comes.  One production round then serves up to PH
+// steps of every chain (a direction takes 4 / pi attempts, so 0.32 rounds per
+// step at best with PH = 4, where a round for one step's trials alone needs
+// more than one).
 //
 // Culling as above, over all G lanes; beads i-2 and i-3 stay in registers.
 // Flagged beads are tested by their own group only.  With one chain per wave
 // (G = 64) a full block of 64 beads whose nearest bead is D from the tip is
 // not scanned again before the tip can have come D - (b + sigma) closer, b
 // per step: rounded down by far more than the arithmetic's error.
+//
+// Bound by VALU issue at N = 256 (0.74-0.81 of the slots, counters) and by the
+// longest surviving chains' serial steps at N = 3000.  MI355X, whole calls,
+// k = 8, lockstep -> queued: N = 256, 2 10^5 chains, 17.0 -> 13.4 ms; N = 3000,
+// 3000 chains, 6.6 -> 3.4 ms.
 // ---------------------------------------------------------------------------
 
 // Smallest of the 64 lanes' non-negative values, in every lane (their bit
@@ -949,11 +955,12 @@ __global__ __launch_bounds__(64) void grow_real_hbm(GrowArgs a)
     grow_real_queue_body<64, true>(a, a.bead_slots + (size_t)blockIdx.x * 3 * a.n_monomers, ring);
 }
 
-// Largest bead count of the LDS-resident kernel, and of the HBM one.  LDS
-// planes fit up to N = 6826, but beyond N ~ 1500 they leave fewer than 4
-// waves per CU, and the HBM planes (8 waves per CU, cached in L2) are faster:
-// measured on MI355X, k = 8, per launch: N = 1024 LDS 15.7 ms / HBM 20.3 ms,
-// N = 2048 30.8 / 28.4, N = 4096 121.7 / 53.2, N = 6144 126.2 / 78.0.
+// Largest bead count with the beads in LDS, beyond which they lie in HBM planes
+// in the workspace (8 waves per CU, the latest 256 beads in LDS, the rest from
+// L2).  LDS would hold N = 6826, but leaves fewer waves: MI355X, k = 8, LDS /
+// HBM: N = 1024, 2 10^4 chains, 5.8 / 5.5 ms; N = 1536, 10^4, 5.0 / 4.1.  The
+// line stays at 1536 all the same, since below it a call needs no bead planes in
+// its workspace (72 MiB there).
 constexpr int kRealLdsMax = 1536;
 int real_max_monomers() { return 16384; }
 
