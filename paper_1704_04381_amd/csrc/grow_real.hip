@@ -43,6 +43,7 @@
 // Putting these together, 0.49 e (b + sigma) >= 11.5 u (b + sigma) + u |tip|
 // suffices, and with |tip| <= (N - 1) b that holds for N <= 4 10^6: a culled
 // bead would also have passed the full test.
+#include "real_skip.hpp"
 #include "rsaw_device.hpp"
 
 namespace rsaw {
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(256) void grow_real_tp_batch(const GrowEntry *tab, 
 // Flagged beads are tested by their own group only.  With one chain per wave
 // (G = 64) a full block of 64 beads whose nearest bead is D from the tip is
 // not scanned again before the tip can have come D - (b + sigma) closer, b
-// per step: rounded down by far more than the arithmetic's error.
+// per step (real_skip.hpp).
 //
 // Bound by VALU issue at N = 256 (0.74-0.81 of the slots, counters) and by the
 // longest surviving chains' serial steps at N = 3000.  MI355X, whole calls,
@@ -628,7 +629,8 @@ __device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *
     double *P = planes + (lane / G) * stride;
     const double b = a.bond_length;
     const double sigma2 = a.sigma2, cull2 = a.cull2;
-    const float reach = sqrtf((float)cull2) * 1.00001f, per_b = 1.0f / (float)b;
+    const double unit = skip_unit(b);
+    const float reach = skip_reach(cull2, unit);
 
     double tx = 0.0, ty = 0.0, tz = 0.0;                       // bead i-1
     double x2 = 0.0, y2 = 0.0, z2 = 0.0, x3 = 0.0, y3 = 0.0, z3 = 0.0; // beads i-2, i-3
@@ -837,9 +839,7 @@ __device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *
                         retest(ub, bb);
                         const auto next_due = [&](double d2, uint64_t u, int b0) {
                             if (u != 0 || b0 + 64 > nbu) return i + 1;
-                            const float d = __builtin_amdgcn_sqrtf(wave_min((float)d2)) * 0.99999f;
-                            const float n = floorf((d - reach) * per_b - 0.01f);
-                            return i + 1 + (n > 0.0f ? (n < 20000.0f ? (int)n : 20000) : 0);
+                            return i + 1 + skip_steps(wave_min((float)(d2 * unit)), reach);
                         };
                         const int na = next_due(da, ua, ba);
                         due[rg] = lane == qa ? na : due[rg];
