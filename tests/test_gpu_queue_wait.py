@@ -1,0 +1,35 @@
+"""No chain of the queued hard-sphere kernel waits in a wave that is busy
+while others are free: an ensemble that fits on the GPU at once takes the
+time of its longest chains, not twice that.  GPU test; calls the HIP library
+through its C ABI.
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_1704_04381_amd as rs
+
+pytestmark = pytest.mark.gpu
+
+
+def _ms(N, k, M, sigma):
+    best = float("inf")
+    for _ in range(12):
+        rs.kernel_timing(True)
+        rs.kernel_time()
+        rs.gen_chains("real", N, k, M, 7, sync=False, bead_diameter=sigma)
+        torch.cuda.synchronize()
+        best = min(best, rs.kernel_time()[0])
+        rs.kernel_timing(False)
+    return best
+
+
+def test_chains_that_fit_at_once_start_at_once():
+    # 2000 and 4000 chains are 500 and 1000 of the 4096 waves the GPU holds, at
+    # most one per SIMD; a chain that waits for another takes the call to twice
+    # the time, so the line lies halfway
+    N, k, sigma = 100, 4, 0.75
+    print(f"[gpu] queue wait N={N} k={k}", flush=True)
+    few, more = _ms(N, k, 2_000, sigma), _ms(N, k, 4_000, sigma)
+    print(f"2000 chains {few:.3f} ms, 4000 chains {more:.3f} ms")
+    assert more < 1.5 * few
