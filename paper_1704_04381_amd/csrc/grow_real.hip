@@ -609,8 +609,10 @@ __host__ __device__ inline int queue_stride(int N, int G)
 }
 
 template <int G, bool HBM>
-__device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *planes, double *ring)
+__device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, uint32_t block, uint32_t blocks,
+                                                     double *planes, double *ring)
 {
+    constexpr uint32_t CPB = 64 / G;
     static_assert(!HBM || G == 64, "global planes hold one chain per wave");
     constexpr int kAhead = 2;
     const int lane = threadIdx.x & 63;
@@ -643,8 +645,19 @@ __device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *
     uint32_t n_mine = 0; // steps with m = t + 1
     uint32_t rd = 0;
     uint64_t c = 0, best = 0;
-    uint64_t next = 0, end = 0; // the wave's chunk of the queue
+    // the wave's share of the queue: to begin with a chain for each group, its
+    // own without asking; the counter holds what was taken of the others
+    const uint32_t resident = blocks * CPB;
+    uint64_t next = (uint64_t)block * CPB;
+    uint64_t end = next + CPB < a.n_chains ? next + CPB : a.n_chains;
+    uint32_t left = a.n_chains > resident ? (uint32_t)(a.n_chains - resident) : 0u; // as last seen
     bool drained = false;
+    // Chains in global memory that end within a few beads (k b / sigma <= 2.25):
+    // the counter would bound them, so that a wave takes half of its share, at
+    // most 8 (N = 3000, sigma = 1, 10^5 chains, k = 1, 1.26 -> 0.57 ms; k = 2, 1.33
+    // -> 1.06; but k = 4, sigma = 0.4, 2 10^4 chains, 32 -> 38, where many chains
+    // live long and the rest should not wait for them).
+    const bool brief = 16.0 * ((double)(k * k) * (b * b)) <= 81.0 * sigma2;
 
     const auto start = [&]() { // the chain's next attempt
         alive = N > 1;
@@ -727,22 +740,28 @@ __device__ __forceinline__ void grow_real_queue_body(const GrowArgs &a, double *
             const uint64_t want = __ballot(!busy && t == 0);
             if (want == 0 || drained) break;
             if (next == end) {
+                if (left == 0) {
+                    drained = true;
+                    break;
+                }
                 // A chain taken and not wanted waits for another of the wave's
-                // groups to end.  So a wave takes what it wants, and a chain for
-                // every group (fewer atomics, 11-14 ns each on the one counter)
-                // only while one for every group that the GPU can hold is left.
-                // Taken without that look, single chains waited for 340 of a
-                // call's 620 us (N = 213, k = 8, 4000 chains; now 450); never
-                // more than wanted, 6 10^4 chains of N = 139, k = 1, which end
-                // after a few steps, took 1.4 times as long.
-                uint32_t take = 64 / G;
-                if constexpr (G < 64)
-                    if (a.n_chains - end < 4096u * (64 / G)) take = (uint32_t)__builtin_popcountll(want);
+                // groups to end (single chains waited 340 of a call's 620 us:
+                // N = 213, k = 8, 4000 chains), so a wave takes what it wants,
+                // and more (fewer atomics, 11-14 ns each on the one counter) only
+                // while plenty are left.
+                uint32_t take = (uint32_t)__builtin_popcountll(want);
+                if constexpr (HBM) {
+                    const uint32_t share = left / (2u * resident);
+                    take = brief && left >= resident ? (share < 2u ? 2u : (share < 8u ? share : 8u)) : take;
+                } else {
+                    if (left >= resident) take = CPB;
+                }
                 unsigned long long v = 0;
                 if (lane == 0) v = atomicAdd(a.queue, (unsigned long long)take);
-                next = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
-                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+                next = resident + (((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
                 end = next + take < a.n_chains ? next + take : a.n_chains;
+                left = (uint32_t)(a.n_chains - end);
                 if (next >= a.n_chains) {
                     drained = true;
                     break;
@@ -946,7 +965,7 @@ template <int G>
 __global__ __launch_bounds__(64) void grow_real_queue(GrowArgs a)
 {
     extern __shared__ double lds[];
-    grow_real_queue_body<G, false>(a, lds, nullptr);
+    grow_real_queue_body<G, false>(a, blockIdx.x, gridDim.x, lds, nullptr);
 }
 
 // Batched launch: block b serves the ensemble whose block range holds b.
@@ -955,15 +974,17 @@ __global__ __launch_bounds__(64) void grow_real_queue_batch(const GrowEntry *tab
                                                             uint64_t base)
 {
     extern __shared__ double lds[];
-    const int e = find_segment(block0, n, base + blockIdx.x);
-    grow_real_queue_body<G, false>(tab[e].a, lds, nullptr);
+    const uint64_t bid = base + blockIdx.x;
+    const int e = find_segment(block0, n, bid);
+    grow_real_queue_body<G, false>(tab[e].a, (uint32_t)(bid - block0[e]), (uint32_t)tab[e].H, lds, nullptr);
 }
 
 // Chains beyond the LDS limit: block s grows its chains in HBM plane region s.
 __global__ __launch_bounds__(64) void grow_real_hbm(GrowArgs a)
 {
     __shared__ double ring[3 * kRing];
-    grow_real_queue_body<64, true>(a, a.bead_slots + (size_t)blockIdx.x * 3 * a.n_monomers, ring);
+    grow_real_queue_body<64, true>(a, blockIdx.x, gridDim.x, a.bead_slots + (size_t)blockIdx.x * 3 * a.n_monomers,
+                                   ring);
 }
 
 // Largest bead count with the beads in LDS, beyond which they lie in HBM planes

@@ -704,10 +704,11 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         }
         Group &G = groups.back();
         gtab[q].a = grow_args(&cfgs[i], o[i], L[i], ws);
-        gtab[q].H = var[i].H;
+        const uint64_t nb = rsaw::variant_blocks(var[i], cfgs[i].n_chains);
+        gtab[q].H = var[i].family == 5 ? (int32_t)nb : var[i].H; // the queued kernel's grid
         gtab[q].S = var[i].S;
         gb0[q] = b;
-        b += rsaw::variant_blocks(var[i], cfgs[i].n_chains);
+        b += nb;
         G.last = q + 1;
         G.blocks = b;
         G.shmem = std::max(G.shmem, var[i].shmem);

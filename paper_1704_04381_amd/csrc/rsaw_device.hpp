@@ -196,7 +196,8 @@ __device__ __forceinline__ void publish_log_w_max_block(const GrowArgs &a, uint6
 }
 
 // One ensemble of a batched launch: its arguments and, for the LDS lattice
-// kernel, its plane length H and chain stride S (words).
+// kernel, its plane length H and chain stride S (words); for the queued
+// hard-sphere kernel its blocks H.
 struct GrowEntry {
     GrowArgs a;
     int32_t H, S;

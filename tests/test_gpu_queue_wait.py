@@ -33,3 +33,13 @@ def test_chains_that_fit_at_once_start_at_once():
     few, more = _ms(N, k, 2_000, sigma), _ms(N, k, 4_000, sigma)
     print(f"2000 chains {few:.3f} ms, 4000 chains {more:.3f} ms")
     assert more < 1.5 * few
+
+
+def test_short_chains_are_not_bound_by_the_queue():
+    # chains of one trial end after a few beads; the queue's counter serves one
+    # atomic per 11 ns at best, so a call that took each chain from it would
+    # need 1.1 ms for 10^5 chains
+    print("[gpu] queue wait N=2000 k=1", flush=True)
+    ms = _ms(2_000, 1, 100_000, 1.0)
+    print(f"10^5 chains {ms:.3f} ms")
+    assert ms < 1.1
