@@ -1045,11 +1045,9 @@ static hipError_t real_shape(int N, int k, int G, int threads, GrowVariant *v)
     return hipSuccess;
 }
 
-// Lanes of the queued kernel for a call, 0 where the lockstep kernel serves it.
-// Few trials and long chains meet dead ends early, which the lockstep kernel
-// pays for to the last step of its wave; and the queued kernel's skipped
-// blocks save more the longer the chain.  Kernel time, lockstep / queued (16,
-// 32, 64 lanes), MI355X, b = sigma = 1:
+// Lanes of the queued kernel for chains of N beads and k trials, 0 where the
+// lockstep kernel serves every call.  Kernel time, lockstep / queued (16, 32, 64
+// lanes), MI355X, b = sigma = 1, 10^5 chains and more (fewer where N is large):
 //   k = 4:  N = 64 1.35 / 1.50 1.98 3.34 ms; N = 100 1.52 / 1.15 1.32 2.06;
 //           N = 160 3.77 / 1.67 1.57 2.25; N = 400 2.76 / 2.07 1.48 1.46
 //   k = 8:  N = 128 2.73 / 3.02 3.28 4.69; N = 144 3.77 / 3.68 3.68 5.19;
@@ -1063,6 +1061,50 @@ static int queue_lanes(int N, int k)
     if (k <= 4) return N < 80 ? 0 : (N < 140 ? 16 : (N < 400 ? 32 : 64));
     if (k <= 8) return N < 144 ? 0 : (N < 280 ? 32 : 64);
     return N < (k <= 16 ? 400 : (k <= 32 ? 500 : 1000)) ? 0 : 64;
+}
+
+// Whether the queued kernel (G lanes) is the faster one for `chains` such
+// chains that share the GPU.  How soon chains end goes with e = k b / sigma, the
+// trials per bead diameter: k = 8, sigma = b ends like k = 4, sigma = b / 2.
+//  - Chains that all fit at up to two waves per SIMD (three with one chain per
+//    wave): the queued step has the shorter serial path, and ends no later.
+//    Queued / lockstep time, 1000 and 4000 chains: N = 100, k = 4 0.77, 0.82;
+//    N = 213, k = 6 0.78, 0.91; N = 256, k = 8 0.98, 1.01; N = 400, k = 8 (1000
+//    and 3000) 0.69, 0.87.
+//  - More chains than that: the queue wins by the steps that dead ends leave
+//    idle in lockstep, more with shorter-lived and longer chains, against a
+//    step that costs more.  `most` is the e up to which it won, by N and the
+//    number of chains.  64,000 chains: N = 100, e = 3.3 0.63, e = 6.7 1.15; N =
+//    180, e = 6.7 0.80, e = 10 1.03; N = 280, k = 8, e = 6.7 0.77, e = 20 1.22.
+//    8000 chains: N = 213, e = 4 0.85, e = 8 1.10; N = 340, e = 8 0.80, e = 20 0.97.
+//  - Beyond N = 256 the lockstep kernel's waves leave the step loop with their
+//    last chain: where all end within a few beads it wins (N = 340, e = 1.3,
+//    16,000 chains, 1.6; N = 500, e = 2, 1.5).
+//  - N >= 500: 0.7 to 0.95 otherwise, but 1.05 where few chains live long
+//    (N = 500, k = 8, sigma = 0.4, 1000 chains).
+// Over 11,000 calls with k = 1..64, N = 80..1536, sigma / b = 0..1.2 and 1000 to
+// 256,000 chains this is 0.6 % behind the faster of the two, the queue for every
+// call 3.4 %, lockstep for every call 33 %.
+static bool queue_serves(int N, int k, double e, uint64_t chains, int G)
+{
+    const bool few = chains <= (G == 64 ? 3072u : 2048u * (64u / (unsigned)G));
+    if (k > 8) {
+        if (N < 500) return k <= 12 || chains >= 6000;
+        return !(N < 700 && few && e > 1.5 * k);
+    }
+    if (N >= 500) return e >= 3.0 && !(N < 700 && few && e > 1.5 * k);
+    if (N >= 400 && e < 2.1) return false;
+    if (few) return true;
+    if (N > 256 && e < 2.0) return false;
+    const uint64_t M = chains;
+    double most = 1e300;
+    if (N < 115) most = M < 24000 ? 3.0 : 4.5;
+    else if (N < 140) most = 5.2;
+    else if (N < 200) most = M < 12000 ? 4.2 : (M < 64000 ? 6.7 : 8.9);
+    else if (N < 250) most = M < 12000 ? 4.6 : (M < 64000 ? 7.5 : 10.0);
+    else if (N < 340) most = M < 8000 ? 4.5 : (M < 24000 ? 7.4 : (M < 64000 ? 8.9 : 9.3));
+    else if (M < 6000) most = 7.0;
+    return e <= most;
 }
 
 // Built-in rule.  Lanes per chain: at least the next power of two >= k (one
@@ -1095,7 +1137,9 @@ hipError_t real_variant(const GrowArgs &a, GrowVariant *v, bool scan)
         return hipSuccess;
     if (!scan) {
         const int G = queue_lanes(N, a.k_trials);
-        if (G && queue_shape(N, G, v) == hipSuccess) return hipSuccess;
+        const double e = a.sigma2 > 0.0 ? a.k_trials * (a.bond_length / sqrt(a.sigma2)) : 1e300;
+        if (G && queue_serves(N, a.k_trials, e, a.n_chains, G) && queue_shape(N, G, v) == hipSuccess)
+            return hipSuccess;
     }
     int need = a.k_trials;
     const int occ = (3 * N + 39) / 40; // ceil(0.075 N)

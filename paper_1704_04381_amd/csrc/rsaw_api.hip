@@ -483,14 +483,18 @@ rsaw_status gen_impl(const rsaw_config *cfg, const rsaw_chain_out *out, rsaw_sum
 
 // Growth-kernel variant (kernel family, template parameters, block shape)
 // of one ensemble, as its launch would choose it; with `scan`, of the
-// kernels whose lane mapping the tuning table holds.
-hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, rsaw::GrowVariant *v, bool scan = false)
+// kernels whose lane mapping the tuning table holds.  `real_chains`: the chains
+// of the hard-sphere ensembles that share its launches, itself included.
+hipError_t ensemble_variant(const rsaw_config *cfg, const EnsLayout &L, uint64_t real_chains, rsaw::GrowVariant *v,
+                            bool scan = false)
 {
     rsaw::GrowArgs probe;
     std::memset(&probe, 0, sizeof(probe));
     probe.n_monomers = cfg->n_monomers;
     probe.k_trials = cfg->k_trials;
-    probe.n_chains = cfg->n_chains;
+    probe.bond_length = cfg->bond_length;
+    probe.sigma2 = cfg->bead_diameter * cfg->bead_diameter;
+    probe.n_chains = L.lattice ? cfg->n_chains : real_chains;
     probe.max_rounds = (cfg->flags & RSAW_RESTART) ? 65536u : 1u;
     const bool i16 = cfg->coord_type == RSAW_I16;
     if (!L.lattice) return rsaw::real_variant(probe, v, scan);
@@ -602,11 +606,14 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
     std::vector<rsaw::GrowVariant> var(n);
     size_t off = 0;
     int max_bins = 0;
+    uint64_t real_chains = 0;
+    for (int32_t i = 0; i < n; ++i)
+        if (cfgs[i].geometry == RSAW_REAL_HS) real_chains += cfgs[i].n_chains;
     for (int32_t i = 0; i < n; ++i) {
         in[i] = outs ? outs[i] : rsaw_chain_out{};
         layout_ensemble(&cfgs[i], in[i], reduce, &off, &L[i]);
         max_bins = std::max(max_bins, L[i].bins);
-        e = ensemble_variant(&cfgs[i], L[i], &var[i]);
+        e = ensemble_variant(&cfgs[i], L[i], real_chains, &var[i]);
         if (e != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "ensemble " + std::to_string(i) + ": no kernel variant");
     }
     // site sets share the GPU's LDS: their tables are sized for all of the
@@ -801,7 +808,7 @@ rsaw_status query_mapping(const rsaw_config *cfg, rsaw_mapping *m)
     size_t off = 0;
     layout_ensemble(cfg, none, false, &off, &L);
     rsaw::GrowVariant v;
-    if (ensemble_variant(cfg, L, &v, true) != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
+    if (ensemble_variant(cfg, L, cfg->n_chains, &v, true) != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
     m->geometry = cfg->geometry;
     m->k_trials = cfg->k_trials;
     m->n_lo = m->n_hi = cfg->n_monomers;
