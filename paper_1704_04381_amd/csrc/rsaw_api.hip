@@ -633,7 +633,13 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
     // same blocks per CU, so it keeps its occupancy instead of running at
     // that of the longest chains in the batch.  Smaller ensembles cannot
     // fill the CUs alone and share one launch per variant, as few launches
-    // as possible.
+    // as possible.  The grid of a queued kernel has no more blocks than stay
+    // resident, so there the chains tell: three times what the GPU holds, as a
+    // launch of its own also waits for its longest chains alone.  Together /
+    // apart: 4 10^4 hard-sphere chains of N = 300 and 200 of N = 1536, 10.4 / 5.9
+    // ms; 6 10^4 chains of 26 neighbours, N = 301 (2.4 times) and 100 of N = 3000,
+    // 2.1 / 3.2; 4 10^4 six-neighbour chains of N = 1100 and 100 of N = 8000, 3.0 /
+    // 4.6.
     int n_cu = 256;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
         n_cu = 256;
@@ -644,9 +650,13 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         order.push_back(i);
         const rsaw::GrowVariant &v = var[i];
         const uint64_t cap = 2048 / (uint64_t)v.threads;
-        const uint64_t slots = v.shmem ? std::min((uint64_t)(163840 / v.shmem), cap) : cap;
-        const uint64_t blocks = rsaw::variant_blocks(v, cfgs[i].n_chains);
-        per_cu[i] = blocks >= slots * (uint64_t)n_cu ? slots : 0;
+        uint64_t slots = v.shmem ? std::min((uint64_t)(163840 / v.shmem), cap) : cap;
+        bool fills = rsaw::variant_blocks(v, cfgs[i].n_chains) >= slots * (uint64_t)n_cu;
+        if (v.max_blocks) {
+            slots = std::min(slots, std::max((uint64_t)1, (uint64_t)v.max_blocks / n_cu));
+            fills = cfgs[i].n_chains >= 3 * (uint64_t)v.max_blocks * v.cpb;
+        }
+        per_cu[i] = fills ? slots : 0;
     }
     auto key = [&](int32_t i) {
         const rsaw::GrowVariant &v = var[i];
