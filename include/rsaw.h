@@ -501,7 +501,7 @@ rsaw_status rsaw_fp64_check(const double *d_a, const double *d_b, double *d_sqrt
 typedef struct {
     int32_t geometry;   /* RSAW_LATTICE_SC, RSAW_REAL_HS or RSAW_LATTICE_26      */
     int32_t k_trials;   /* k of the calls the entry applies to (6 or 26 on the    */
-                        /* lattices)                                              */
+                        /* lattices); 0 from a query: no call runs with it        */
     int32_t n_lo, n_hi; /* chain lengths N (monomers) covered, inclusive          */
     int32_t lanes;      /* lanes per chain                                        */
     int32_t threads;    /* threads per block                                      */
@@ -557,9 +557,11 @@ rsaw_status rsaw_mapping_list(rsaw_mapping *out, int32_t capacity, int32_t *coun
  * rsaw_mapping_query — the mapping a rsaw_gen_chains call with `cfg` would
  * launch its group kernel with, written to the host struct *m (n_lo =
  * n_hi = cfg->n_monomers).  Host-only, no device call.  Where the built-in
- * rule serves long chains with a kernel that has no mapping (the site set of
- * the lattices, the queued hard-sphere kernel up to N = 1536), this is the
- * built-in mapping of the kernel that a table entry would select there.
+ * rule serves the call with a kernel that has no mapping (the site set of
+ * the lattices, the queued hard-sphere kernel up to N = 1536), lanes, threads
+ * and lds_bytes are those of the kernel that a table entry would select
+ * there, and k_trials is 0: the call does not run with them, and
+ * rsaw_mapping_set refuses the struct as it is.
  * Kernels without a
  * group mapping report lanes = 1 (one lane per chain: lattice N <= 64, exact
  * weights) or lanes = 64 with lds_bytes = 0 (hard spheres beyond N = 1536,
@@ -584,9 +586,12 @@ rsaw_status rsaw_mapping_query(const rsaw_config *cfg, rsaw_mapping *m);
  *   reps       timed calls per candidate (1..100), after one untimed call.
  *   chosen     host array of n_buckets, or NULL: the mapping each bucket
  *              runs with afterwards (the winner, or the mapping in force; the
- *              built-in one, unchanged, where N has no group kernel).
+ *              built-in one, unchanged, where N has no group kernel).  Where
+ *              a kernel without a mapping is in force and stays, k_trials is
+ *              0, as rsaw_mapping_query reports it.
  *   best_ms    host array of n_buckets, or NULL: the winner's mean time per
- *              call (growth and reduction, HIP events on `stream`).
+ *              call (growth and reduction, HIP events on `stream`); with
+ *              k_trials 0, that of the kernel in force.
  *   stream     hipStream_t or NULL.
  *
  * Each probe is a full rsaw_gen_chains call (growth into the library's
@@ -594,7 +599,9 @@ rsaw_status rsaw_mapping_query(const rsaw_config *cfg, rsaw_mapping *m);
  * timed one after another on `stream`, which this call synchronises; other
  * threads' calls are unaffected while it runs and pick up the installed
  * entries afterwards.  The winners go into the tuning table as by
- * rsaw_mapping_set.
+ * rsaw_mapping_set: an entry replaces the built-in rule for every call of its
+ * geometry, k and N, also where the rule would look at the number of chains,
+ * restarts or sigma, so probe with those of the calls that it is meant for.
  * Errors: RSAW_E_INVALID for a bad base config (as rsaw_gen_chains), NULL
  * or non-increasing n_edges, n_buckets or reps out of range;
  * RSAW_E_DEVICE / RSAW_E_NOMEM for runtime failures (entries of buckets

@@ -571,8 +571,10 @@ def load_mappings(path) -> int:
 
 
 def mapping_query(cfg: rsaw_config) -> dict:
-    """The mapping a call with cfg would launch with (rsaw_mapping_query;
-    host-only)."""
+    """The mapping a call with cfg would launch its group kernel with
+    (rsaw_mapping_query; host-only).  `k_trials` is 0 where the call runs on
+    a kernel without a mapping: the rest is then what a table entry would
+    replace."""
     m = rsaw_mapping()
     _check(load().rsaw_mapping_query(C.byref(cfg), C.byref(m)))
     return _mapping_dict(m)
@@ -581,7 +583,8 @@ def mapping_query(cfg: rsaw_config) -> dict:
 def autotune(geometry, k, n_edges, n_chains, *, seed=1, reps=3, stream=None, **cfg_kw) -> list[dict]:
     """Time every legal lane mapping at each bucket edge and install the
     fastest (rsaw_autotune).  Returns one dict per bucket: the chosen
-    mapping plus its mean time per call, `ms`."""
+    mapping plus its mean time per call, `ms` (with `k_trials` 0, the time of
+    the kernel without a mapping that stays in force)."""
     import torch
 
     edges = [int(n) for n in n_edges]

@@ -809,18 +809,22 @@ struct ForceMapping {
 };
 
 // Mapping of the group kernel for cfg: the tuning table's, or the built-in
-// rule's (host-only).  Where the built-in rule takes the site set instead of
-// a group kernel, this is the mapping a table entry would replace.
+// rule's (host-only).  Where the built-in rule takes a kernel without a mapping
+// (site set, queued hard spheres), this is the mapping a table entry would
+// replace, and its k_trials is 0: it applies to no call, and rsaw_mapping_set
+// refuses it.
 rsaw_status query_mapping(const rsaw_config *cfg, rsaw_mapping *m)
 {
     rsaw_chain_out none{};
     EnsLayout L;
     size_t off = 0;
     layout_ensemble(cfg, none, false, &off, &L);
-    rsaw::GrowVariant v;
-    if (ensemble_variant(cfg, L, cfg->n_chains, &v, true) != hipSuccess) return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
+    rsaw::GrowVariant v, used;
+    if (ensemble_variant(cfg, L, cfg->n_chains, &v, true) != hipSuccess ||
+        ensemble_variant(cfg, L, cfg->n_chains, &used) != hipSuccess)
+        return fail(RSAW_E_UNSUPPORTED, "no kernel variant");
     m->geometry = cfg->geometry;
-    m->k_trials = cfg->k_trials;
+    m->k_trials = used.family == 4 || used.family == 5 ? 0 : cfg->k_trials;
     m->n_lo = m->n_hi = cfg->n_monomers;
     // register lattice (family 0) and 26-neighbour lane kernel: one lane per chain
     m->lanes = v.family == 0 || (v.family == 3 && v.p0 == 1) ? 1 : v.p0;
@@ -1298,7 +1302,7 @@ rsaw_status rsaw_autotune(const rsaw_config *base, const int32_t *n_edges, int32
         // first: a candidate replaces it only when it is at least
         // kTuneMargin faster, so that timing noise does not move ensembles
         // away from a mapping that also suits co-scheduled launches
-        const rsaw_mapping cur = win;
+        const rsaw_mapping cur = win; // k_trials 0: a kernel without a mapping
         double cur_ms = -1.0;
         if (cur.lanes >= 2) {
             st = time_calls(c, &cur_ms);
