@@ -300,8 +300,8 @@ void rsaw_batch_plan_destroy(rsaw_batch_plan *plan);
  * requests.  It launches each batch with rsaw_gen_batch on a free stream,
  * so a new batch starts while others run.  With size classes (large_ms), at most one large request is in
  * flight and a batch holds at most one, while small requests skip past
- * queued large ones; the size estimate is a per-chain cost model (N^2 scan
- * work, per geometry and k) used for scheduling only.  A completion thread
+ * queued large ones; the size estimate is a per-chain cost model (by geometry,
+ * N, and for hard spheres k, b and sigma) used for scheduling only.  A completion thread
  * per stream retires the batch's tickets.  Each result is bit-identical to
  * a stand-alone rsaw_gen_chains call with the same configuration, whatever
  * the mix it was served in.

@@ -37,6 +37,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "request_cost.hpp"
 #include "rsaw.h"
 #include "rsaw_reduce.hpp"
 
@@ -72,19 +73,6 @@ struct Slot {
 // Device workspace bytes a request holds while its batch runs.
 size_t request_bytes(const rsaw_config &c) { return rsaw::batch_entry_bytes(&c); }
 
-// Estimated growth time of a request alone on the device, in ms, for the
-// size classes only (it never affects a result).  A chain's scan work grows
-// as N^2; the constants are per-chain times at N = 64 on one MI355X: 0.2 ns
-// (lattice, registers), 0.65 ns (26-neighbour lattice), 1 ns per trial
-// (hard spheres), and 3x on the lattices beyond N = 64 (group kernels).
-double estimate_ms(const rsaw_config &c)
-{
-    const double n = c.n_monomers / 64.0;
-    double ns = c.geometry == RSAW_REAL_HS ? 1.0 * c.k_trials : (c.geometry == RSAW_LATTICE_26 ? 0.65 : 0.2);
-    if (c.geometry != RSAW_REAL_HS && c.n_monomers > 64) ns *= 3.0;
-    return (double)c.n_chains * ns * n * n * 1e-6;
-}
-
 } // namespace
 
 struct rsaw_server {
@@ -102,7 +90,7 @@ struct rsaw_server {
     std::string error;
     size_t budget = 0; // workspace bytes of each stream
 
-    bool is_large(const rsaw_config &c) const { return p.large_ms >= 0.0 && estimate_ms(c) > large_ms(); }
+    bool is_large(const rsaw_config &c) const { return p.large_ms >= 0.0 && rsaw::estimate_ms(c) > large_ms(); }
     double large_ms() const { return p.large_ms > 0.0 ? p.large_ms : 2.0; }
 
     void fail_batch(Slot &sl, rsaw_status st)
