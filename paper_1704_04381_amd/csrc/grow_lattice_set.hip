@@ -83,6 +83,12 @@ __device__ __forceinline__ uint32_t or8(uint32_t v)
     return v;
 }
 
+// Longest chain whose scanning kernels keep one word per monomer, and so heed a
+// lowered byte box.  Beyond it the box would send nearly every chain to
+// replay_chain, N^2 steps on eight lanes (200 chains of N = 10000, 3.2 ms, took
+// 1.6 s), where no result depends on it.
+constexpr int kSetBoxMaxN = 4096;
+
 // Buckets a lookup visits before it gives up.
 constexpr int kSetProbes = 64;
 constexpr uint32_t kSetSpare = 64 * 8; // bytes behind a block's tables: one entry per lane
@@ -328,6 +334,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
     uint2 *spare = (uint2 *)(set_lds + gpw * TB) + lane;
     const int N = a.n_monomers;
     const uint32_t chunk = set_chunk(a.n_chains, gpw, NB);
+    const int box = N <= kSetBoxMaxN ? a.byte_box : 0;
 
     // this lane's candidate: the axis' field mask and the addend of its move
     const bool cand = Z26 || t < 6;
@@ -398,7 +405,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
             // extremes between the looks lie within 8 of these; the unwrapped
             // range starts on a block boundary
             bool over = cmax + 8 - ((cmin - 8) & ~3) >= period - 1;
-            over = over || (a.byte_box > 0 && (cmax >= a.byte_box || -cmin >= a.byte_box));
+            over = over || (box > 0 && (cmax >= box || -cmin >= box));
             over = over || full;
             full = false;
             const uint64_t ob = __builtin_amdgcn_ballot_w64(busy && over);
