@@ -530,10 +530,12 @@ rsaw_status rsaw_mapping_set(const rsaw_mapping *m);
  * group itself, without its site set, in the kernel of long chains).  Each
  * format has its own edge (at most 127, 62 and 254; the site set's is its
  * period); edge = 0 (the default) uses those, 1..127 lowers every edge to at
- * most that value, which only sends more chains through the regrowth.  Beyond
- * N = 4096, where no kernel keeps one word per monomer, it has no effect.
- * Results never depend on it: every chain is bit-identical either way.  Process-wide; applies
- * to calls enqueued after it.  Host-only.
+ * most that value, which only sends more chains through the regrowth.  The site
+ * set heeds values below 62 only, where its regrowth of chains beyond a few
+ * hundred monomers takes far longer than the call does without: for tests.
+ * Beyond N = 4096, where no kernel keeps one word per monomer, it has no effect.
+ * Results never depend on it: every chain is bit-identical either way.
+ * Process-wide; applies to calls enqueued after it.  Host-only.
  * Errors: RSAW_E_INVALID unless 0 <= edge <= 127.
  */
 rsaw_status rsaw_set_byte_box(int32_t edge);

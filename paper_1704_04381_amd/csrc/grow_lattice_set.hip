@@ -83,12 +83,6 @@ __device__ __forceinline__ uint32_t or8(uint32_t v)
     return v;
 }
 
-// Longest chain whose scanning kernels keep one word per monomer, and so heed a
-// lowered byte box.  Beyond it the box would send nearly every chain to
-// replay_chain, N^2 steps on eight lanes (200 chains of N = 10000, 3.2 ms, took
-// 1.6 s), where no result depends on it.
-constexpr int kSetBoxMaxN = 4096;
-
 // Buckets a lookup visits before it gives up.
 constexpr int kSetProbes = 64;
 constexpr uint32_t kSetSpare = 64 * 8; // bytes behind a block's tables: one entry per lane
@@ -334,7 +328,6 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
     uint2 *spare = (uint2 *)(set_lds + gpw * TB) + lane;
     const int N = a.n_monomers;
     const uint32_t chunk = set_chunk(a.n_chains, gpw, NB);
-    const int box = N <= kSetBoxMaxN ? a.byte_box : 0;
 
     // this lane's candidate: the axis' field mask and the addend of its move
     const bool cand = Z26 || t < 6;
@@ -405,7 +398,7 @@ __device__ __forceinline__ void grow_lattice_set_body(const GrowArgs &a, uint32_
             // extremes between the looks lie within 8 of these; the unwrapped
             // range starts on a block boundary
             bool over = cmax + 8 - ((cmin - 8) & ~3) >= period - 1;
-            over = over || (box > 0 && (cmax >= box || -cmin >= box));
+            over = over || (a.byte_box > 0 && (cmax >= a.byte_box || -cmin >= a.byte_box));
             over = over || full;
             full = false;
             const uint64_t ob = __builtin_amdgcn_ballot_w64(busy && over);
@@ -721,6 +714,13 @@ hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, Gro
     return hipSuccess;
 }
 
+// The byte box (rsaw_set_byte_box) that the set heeds.  A lowered one sends chains
+// to replay_chain, so that tests reach it; but N^2 steps on eight lanes take long
+// (2000 chains of N = 3000 at an edge of 127: 251 ms; 1.1 without), and the set
+// keeps no bytes.  So it heeds only edges below every format's own (62 is the
+// smallest), and none beyond N = 4096, where no kernel keeps one word per monomer.
+int32_t lattice_set_box(int N, int32_t edge) { return N <= 4096 && edge < 62 ? edge : 0; }
+
 template <bool Z26, typename CT>
 static hipError_t launch_set(const GrowArgs &a, const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0,
                              int n, uint64_t blocks, size_t shmem, hipStream_t s)
@@ -730,11 +730,13 @@ static hipError_t launch_set(const GrowArgs &a, const GrowVariant &v, const Grow
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
         if (e != hipSuccess) return e;
     }
+    GrowArgs one = a;
+    one.byte_box = lattice_set_box(a.n_monomers, a.byte_box);
     return launch_sliced(blocks, 64, [&](uint64_t b0, uint32_t nb) {
         if (tab)
             hipLaunchKernelGGL((grow_lattice_set_batch<Z26, CT>), dim3(nb), dim3(64), shmem, s, tab, block0, n, b0);
         else
-            hipLaunchKernelGGL((grow_lattice_set<Z26, CT>), dim3(nb), dim3(64), shmem, s, a, (uint32_t)v.H,
+            hipLaunchKernelGGL((grow_lattice_set<Z26, CT>), dim3(nb), dim3(64), shmem, s, one, (uint32_t)v.H,
                                (uint32_t)v.S);
     });
 }

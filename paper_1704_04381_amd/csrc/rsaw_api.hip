@@ -41,6 +41,7 @@ hipError_t launch_real_batch(const GrowVariant &v, const GrowEntry *tab, const u
                              uint64_t blocks, size_t shmem, hipStream_t s);
 int lattice26_max_monomers();
 hipError_t lattice_set_variant(int N, uint64_t n_chains, bool z26, bool i16, GrowVariant *v);
+int32_t lattice_set_box(int N, int32_t edge);
 hipError_t lattice26_variant(const GrowArgs &a, bool exact, bool i16, GrowVariant *v, bool scan);
 hipError_t launch_grow_lattice26(const GrowArgs &a, bool exact, bool i16, hipStream_t s);
 hipError_t launch_lattice26_batch(const GrowVariant &v, const GrowEntry *tab, const uint64_t *block0, int n,
@@ -721,6 +722,7 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
         }
         Group &G = groups.back();
         gtab[q].a = grow_args(&cfgs[i], o[i], L[i], ws);
+        if (var[i].family == 4) gtab[q].a.byte_box = rsaw::lattice_set_box(cfgs[i].n_monomers, gtab[q].a.byte_box);
         const uint64_t nb = rsaw::variant_blocks(var[i], cfgs[i].n_chains);
         gtab[q].H = var[i].family == 5 ? (int32_t)nb : var[i].H; // the queued kernel's grid
         gtab[q].S = var[i].S;

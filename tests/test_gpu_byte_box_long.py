@@ -1,5 +1,6 @@
-"""rsaw_set_byte_box beyond N = 4096, where no kernel keeps one word per monomer:
-it changes neither results nor the time of a call.  GPU test; calls the HIP
+"""rsaw_set_byte_box and the site set: beyond N = 4096, where no kernel keeps one
+word per monomer, and at edges that some format keeps anyway, it changes neither
+results nor the time of a call.  GPU test; calls the HIP
 library through its C ABI.
 """
 import numpy as np
@@ -30,11 +31,14 @@ def _run(geo, k, N, M):
     return best, {n: t.cpu().numpy() for n, t in out.items()}
 
 
-@pytest.mark.parametrize("geo,k,N,M", [("lattice", 6, 5_000, 9), ("lattice26", 26, 4_500, 5)])
-def test_no_effect_on_long_chains(geo, k, N, M):
-    print(f"[gpu] byte box {geo} N={N}", flush=True)
+@pytest.mark.parametrize("geo,k,N,M,edge", [
+    ("lattice", 6, 5_000, 9, 60), ("lattice26", 26, 4_500, 5, 60),
+    ("lattice", 6, 3_000, 60, 127), ("lattice26", 26, 2_048, 60, 62),
+])
+def test_no_effect_on_the_site_set(geo, k, N, M, edge):
+    print(f"[gpu] byte box {geo} N={N} edge={edge}", flush=True)
     free, ref = _run(geo, k, N, M)
-    rs.set_byte_box(60)
+    rs.set_byte_box(edge)
     boxed, out = _run(geo, k, N, M)
     for name in ref:
         np.testing.assert_array_equal(out[name], ref[name], err_msg=name)
