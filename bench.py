@@ -75,11 +75,15 @@ def lattice_alg_ops_per_chain(N: int) -> int:
     each (L1 distance, neighbour flag, direction code, mask insert); one
     eighth of a Philox4x32-10 block, the 16 bits the pick consumes (10
     rounds x 6 operations / 8, rounded up to 8); and 10 operations to
-    count, pick and apply the move and tally m_i for log W.  The kernels' pair
-    test takes 2 operations, so their rate in this model's operations can
-    exceed the issue rate.
+    count, pick and apply the move and tally m_i for log W.
     """
     return sum(4 * (i // 2) + 8 + 10 for i in range(1, N))
+
+
+def lattice_ops_per_chain(N: int) -> int:
+    """The same with the pair test of the register kernels, which takes 2
+    operations (L1 distance, direction insert): what they are priced at."""
+    return sum(2 * (i // 2) + 8 + 10 for i in range(1, N))
 
 
 # LDS bandwidth of the chip: 128 bytes per clock per CU, 256 CUs, 2.4 GHz.
@@ -149,48 +153,40 @@ def site_set_lds_bytes_per_chain(N: int, lookups: int) -> int:
 
 
 def path_model(w) -> dict:
-    """Growth kernel of a workload (as the built-in rules choose it), its
-    algorithmic VALU lane-operations and LDS bytes per launch, and the VALU
-    peak it is priced against."""
-    geo, N, M = w["geometry"], w["N"], w["n_chains"]
+    """Growth kernel of a workload, its algorithmic VALU lane-operations and
+    LDS bytes per launch, and the VALU peak it is priced against.  The library
+    says whether the call runs on a kernel without a lane mapping (site set,
+    queued hard spheres)."""
+    import paper_1704_04381_amd as rs
+
+    geo, N, M, k = w["geometry"], w["N"], w["n_chains"], w["k"]
+    cfg = rs.make_config(geo, N, k, M, w["seed"], coord=w["coord"], bond_length=w.get("bond_length", 1.0),
+                         bead_diameter=w.get("bead_diameter", 1.0), exact_w=w.get("exact_w", False),
+                         restart=w.get("restart", False))
+    q = rs.mapping_query(cfg)
     vgprs = "chain history in VGPRs: no LDS traffic"
-    buckets = "one bucket read per lookup, one entry written per step"
+    if geo == "real":
+        hbm = N > 1536
+        return dict(kernel="grow_real_hbm" if hbm else "grow_real_tp" if q["k_trials"] else "grow_real_queue",
+                    kernel_file="grow_real.hip",
+                    ops=real_alg_ops_per_chain(N, k) * M, peak=VALU_PEAK_FP64_TOPS, int_path=False,
+                    lds_bytes=0.0 if hbm else real_lds_bytes_per_chain(N) * M,
+                    lds_note="beads in HBM planes" if hbm else "beads read once per step")
+    if q["k_trials"] == 0:
+        sites, lookups = (6, 6) if geo == "lattice" else (26, 8)
+        return dict(kernel="grow_lattice_set", kernel_file="grow_lattice_set.hip",
+                    ops=site_set_ops_per_chain(N, sites) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
+                    lds_bytes=site_set_lds_bytes_per_chain(N, lookups) * M,
+                    lds_note="one bucket read per lookup, one entry written per step")
+    one = q["lanes"] == 1
     if geo == "lattice":
-        if N > 2048 or (N > 1024 and M >= 4096):
-            return dict(kernel="grow_lattice_set", kernel_file="grow_lattice_set.hip",
-                        ops=site_set_ops_per_chain(N, 6) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                        lds_bytes=site_set_lds_bytes_per_chain(N, 6) * M, lds_note=buckets)
-        reg = N <= 64 or w.get("exact_w", False)
-        return dict(kernel="grow_lattice_reg" if reg else "grow_lattice_grp",
-                    kernel_file="grow_lattice.hip" if reg else "grow_lattice_lds.hip",
-                    ops=lattice_alg_ops_per_chain(N) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                    lds_bytes=0.0, lds_note=vgprs)
-    if geo == "lattice26":
-        if N > 300:
-            return dict(kernel="grow_lattice_set", kernel_file="grow_lattice_set.hip",
-                        ops=site_set_ops_per_chain(N, 26) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                        lds_bytes=site_set_lds_bytes_per_chain(N, 8) * M, lds_note=buckets)
-        return dict(kernel="grow_lattice26_lane" if N <= 64 else "grow_lattice26_grp",
-                    kernel_file="grow_lattice26.hip",
-                    ops=lattice26_alg_ops_per_chain(N) * M, peak=VALU_PEAK_INT32_TOPS, int_path=True,
-                    lds_bytes=0.0, lds_note=vgprs)
-    k = w["k"]
-    queued = N >= (80 if k <= 4 else 144 if k <= 8 else 400 if k <= 16 else 500 if k <= 32 else 1000)
-    hbm = N > 1536
-    return dict(kernel="grow_real_hbm" if hbm else "grow_real_queue" if queued else "grow_real_tp",
-                kernel_file="grow_real.hip",
-                ops=real_alg_ops_per_chain(N, k) * M, peak=VALU_PEAK_FP64_TOPS, int_path=False,
-                lds_bytes=0.0 if hbm else real_lds_bytes_per_chain(N) * M,
-                lds_note="beads in HBM planes" if hbm else "beads read once per step")
-
-
-def lattice_lds_bytes_per_chain(N: int) -> int:
-    """Algorithmic LDS bytes of one long lattice chain in LDS (one 4-byte
-    word per monomer up to N = 2048, two beyond): per step i the floor(i/2)
-    monomers of the tip's opposite parity are read once, and the new monomer
-    is written."""
-    w = 4 if N <= 2048 else 8
-    return sum(w * (i // 2) + w for i in range(1, N))
+        kernel, file = ("grow_lattice_reg", "grow_lattice.hip") if one else ("grow_lattice_grp", "grow_lattice_lds.hip")
+        ops = lattice_ops_per_chain(N) * M
+    else:
+        kernel, file = "grow_lattice26_lane" if one else "grow_lattice26_grp", "grow_lattice26.hip"
+        ops = lattice26_alg_ops_per_chain(N) * M
+    return dict(kernel=kernel, kernel_file=file, ops=ops, peak=VALU_PEAK_INT32_TOPS, int_path=True, lds_bytes=0.0,
+                lds_note=vgprs)
 
 
 def roofline_object(pm: dict, kernel_ms: float, workload: str) -> dict:

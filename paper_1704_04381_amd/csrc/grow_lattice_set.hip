@@ -42,9 +42,11 @@
 // Sums over the placed monomers come from the bitmaps when a chain ends, in
 // the pass that clears the table for the next one.
 //
-// Bound by the latency of a step (about 750 cycles: one dependent LDS read,
-// 40 % of it, and 62 vector instructions) at the number of chains whose tables
-// fit in a CU's LDS.  MI355X, whole calls, scan of the history with 64 lanes or
+// Bound by the latency of a step at the number of chains whose tables fit in a
+// CU's LDS.  N = 2048, 10^5 chains, six per wave and five waves per CU (counters):
+// 1050 cycles, 92 vector and 4.2 LDS instructions per step of a wave, its share of
+// the Philox blocks, chain ends and lookups beyond the home bucket included; the
+// vector units issue 0.44 of the time.  MI355X, whole calls, scan of the history with 64 lanes or
 // in LDS -> set: N = 2048, 10^5 chains, 16.9 -> 9.6 ms; N = 10000, 5000
 // chains, 81.9 -> 6.7 ms, where the longest chain's 10^4 steps alone take 3 ms.
 //

@@ -665,8 +665,8 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
     };
     // within a launch the longest chains first: blocks start in this order, and a
     // block of long chains started last would run on alone while the GPU empties
-    // (256 ensembles of both geometries, index order -> this: 4.20 -> 3.80 ms;
-    // 222 of them 2.77 -> 2.41; 31, which start at once anyway, 0.68 either way)
+    // (calls of 256 ensembles of both geometries, index order -> this: 3.88 -> 3.46
+    // ms; 222 of them 3.41 -> 3.08; 31 0.82 -> 0.65)
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
         const auto kx = key(x), ky = key(y);
         return kx != ky ? kx < ky : cfgs[x].n_monomers > cfgs[y].n_monomers;
