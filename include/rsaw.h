@@ -34,6 +34,11 @@
  *     caller's after rsaw_set_workspace), so calls on the same stream are
  *     ordered by that stream.  Calls on one stream must come from one host
  *     thread at a time (they share that workspace and its staging buffer).
+ *   - Long chains (lattice beyond N = 1024, with restarts 512; 26 neighbours
+ *     from N = 301; hard spheres from N = 80) mostly run in kernels whose blocks
+ *     fill the GPU and stay until the call's chains run out: a call on another
+ *     stream may then wait for that call's end.  rsaw_server_* keeps room for
+ *     its other streams.
  */
 #ifndef RSAW_H
 #define RSAW_H
@@ -297,8 +302,10 @@ void rsaw_batch_plan_destroy(rsaw_batch_plan *plan);
  * (what rsaw_workspace_size reports for the configuration with a reduction
  * and no per-chain outputs, plus its descriptor-table entries, under 1 KiB)
  * fit in a stream's workspace and the batch holds at most max_batch
- * requests.  It launches each batch with rsaw_gen_batch on a free stream,
- * so a new batch starts while others run.  With size classes (large_ms), at most one large request is in
+ * requests.  It launches each batch as rsaw_gen_batch does on a free stream,
+ * so a new batch starts while others run; with more than one stream, a batch
+ * estimated above large_ms (2 ms where that is 0 or less) leaves part of the GPU
+ * to the others.  With size classes (large_ms), at most one large request is in
  * flight and a batch holds at most one, while small requests skip past
  * queued large ones; the size estimate is a per-chain cost model (by geometry,
  * N, and for hard spheres k, b and sigma) used for scheduling only.  A completion thread

@@ -578,6 +578,22 @@ struct PlannedBatch {
     BatchLaunch B;
 };
 
+// A queued kernel's waves keep their LDS and registers until its chains run out,
+// so a launch that fills the GPU makes the launches of other streams wait for its
+// end, where a grid of one block per few chains lets them in between its blocks.
+// `beside` others it takes at most 5/8 of the LDS and two waves per SIMD: the rest
+// holds blocks of any other kernel (four waves of up to 168 VGPRs, 48 KiB).  MI355X,
+// lattice calls of 10^4 chains (N = 256) beside 1.5 10^6 hard-sphere chains (N =
+// 256): 0.2 ms each, 87 beside a launch that fills the GPU (11/16: 114; 3/4: 108),
+// which takes 125 ms instead of 98 (127 with one block per few chains).  Two
+// streams of served requests, 40 per second: p50 1.6 ms, else 15; p99 689, else
+// 545 (862 and p50 4.2 with one block per few chains).
+uint32_t blocks_beside(uint32_t max_blocks)
+{
+    const uint32_t most = 256u * 8u, part = max_blocks / 8u * 5u;
+    return part < most ? part : most;
+}
+
 // Batched body: every ensemble's growth shares one launch per kernel
 // variant, and the reductions three launches in all.
 // With `plan` set, nothing is enqueued: the workspace is the plan's own
@@ -585,7 +601,7 @@ struct PlannedBatch {
 // description goes to *plan.
 rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int32_t n,
                        rsaw_summary *d_summaries, double *const *d_hist_w, uint64_t *const *d_hist_n,
-                       void *stream, PlannedBatch *plan = nullptr)
+                       void *stream, PlannedBatch *plan = nullptr, bool beside = false)
 {
     g_last_error.clear();
     if (n < 0) return fail(RSAW_E_INVALID, "n must be >= 0");
@@ -627,6 +643,9 @@ rsaw_status batch_impl(const rsaw_config *cfgs, const rsaw_chain_out *outs, int3
             rsaw::lattice_set_variant(cfgs[i].n_monomers, set_chains, var[i].p1 != 0, var[i].p2 != 0, &var[i]) !=
                 hipSuccess)
             return fail(RSAW_E_UNSUPPORTED, "ensemble " + std::to_string(i) + ": no kernel variant");
+    if (beside)
+        for (int32_t i = 0; i < n; ++i)
+            if (var[i].max_blocks) var[i].max_blocks = blocks_beside(var[i].max_blocks);
     // ensembles with chains, grouped by variant.  A launch gives every block the largest LDS of its ensembles.
     // An ensemble that fills the GPU by itself (at least one block per slot
     // that its own LDS leaves on every CU: 160 KiB / shmem per CU, capped at
@@ -900,6 +919,13 @@ rsaw_status reserve_staging(hipStream_t s, size_t bytes)
     void *stage = nullptr;
     hipEvent_t done = nullptr;
     return staging(dev, s, bytes, &stage, &done);
+}
+
+// rsaw_gen_batch without per-chain outputs; with `beside`, leaving room for the
+// launches of other streams.
+rsaw_status serve_batch(const rsaw_config *cfgs, int32_t n, rsaw_summary *d_summaries, hipStream_t s, bool beside)
+{
+    return batch_impl(cfgs, nullptr, n, d_summaries, nullptr, nullptr, (void *)s, nullptr, beside);
 }
 
 // Forget the (current device, s) entry: free its internal workspace, its

@@ -61,11 +61,13 @@ hipError_t launch_reduce_batch(const ReduceEntry *tab, const uint64_t *block0, i
 
 // Serving-loop admission: device workspace of one ensemble in a batch (its
 // regions and table entries), the fixed bytes a batch adds, the staging
-// bytes of a batch of n, and an early reservation of a stream's staging.
+// bytes of a batch of n, an early reservation of a stream's staging, and the
+// launch of a batch.
 size_t batch_entry_bytes(const rsaw_config *cfg);
 constexpr size_t kBatchFixedBytes = 2048;
 size_t batch_stage_bytes(int n);
 rsaw_status reserve_staging(hipStream_t s, size_t bytes);
+rsaw_status serve_batch(const rsaw_config *cfgs, int32_t n, rsaw_summary *d_summaries, hipStream_t s, bool beside);
 rsaw_status release_stream(hipStream_t s);
 
 hipError_t launch_reduce_init(unsigned long long *lmax_bits, int32_t *status,

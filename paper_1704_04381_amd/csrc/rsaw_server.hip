@@ -1,6 +1,6 @@
 // Serving loop of librsaw (declared in include/rsaw.h): requests (one
 // ensemble each) are queued by rsaw_server_submit, a scheduler thread forms
-// batches from the queue head and launches each with rsaw_gen_batch on one
+// batches from the queue head and launches each as rsaw_gen_batch does on one
 // of S streams, and a completion thread per stream waits for the batch's
 // event, copies the summaries out and retires the tickets.
 //
@@ -21,7 +21,9 @@
 // arrival order, each sharing the GPU only with batches of small requests,
 // which skip past queued large ones.  Two large requests run side by side
 // would each take about twice as long, so the tail latency is set by
-// serving them in series, while the small ones keep the concurrency.
+// serving them in series, while the small ones keep the concurrency.  For that
+// a batch estimated above large_ms leaves room on the GPU where there is more
+// than one stream (blocks_beside in rsaw_api.hip).
 // Every result is that of a stand-alone rsaw_gen_chains call (batched
 // growth and reduction are bit-identical to single calls).
 #include <hip/hip_runtime.h>
@@ -177,8 +179,12 @@ struct rsaw_server {
             free_slot->tickets = batch;
             lk.unlock();
             // the launch itself runs outside the lock; only this thread launches
-            rsaw_status st = rsaw_gen_batch(cfgs.data(), nullptr, (int32_t)cfgs.size(), free_slot->d_summ,
-                                            nullptr, nullptr, free_slot->stream);
+            // a long batch leaves room on the GPU for the batches of other streams
+            double ms = 0.0;
+            for (const rsaw_config &c : cfgs) ms += rsaw::estimate_ms(c);
+            const bool beside = slots.size() > 1 && ms > large_ms();
+            rsaw_status st = rsaw::serve_batch(cfgs.data(), (int32_t)cfgs.size(), free_slot->d_summ,
+                                               free_slot->stream, beside);
             hipError_t e = hipSuccess;
             if (st == RSAW_OK)
                 e = hipMemcpyAsync(free_slot->h_summ, free_slot->d_summ, cfgs.size() * sizeof(rsaw_summary),
